@@ -548,7 +548,6 @@ tp_status tp_gauge_create(tp_ctx ctx, const void* links, int32_t where, tp_gauge
       g->u4_f = static_cast<float2*>(dev_alloc(ctx, lb / 2));
       g->w_d = static_cast<double2*>(dev_alloc(ctx, size_t(2) * 9 * L.V2 * sizeof(double2)));
       g->poly = static_cast<double2*>(dev_alloc(ctx, size_t(2) * 9 * L.Vs2 * sizeof(double2)));
-      g->canon_ax = static_cast<double2*>(dev_alloc(ctx, lb));
       int* flags = static_cast<int*>(dev_alloc(ctx, 4 * sizeof(int)));
       int hf[4] = {1, 1, 1, 1};
       try {
@@ -589,7 +588,6 @@ tp_status tp_gauge_destroy(tp_gauge g) {
     dev_free(ctx, g->u4_d);
     dev_free(ctx, g->u4_f);
     dev_free(ctx, g->w_d);
-    dev_free(ctx, g->canon_ax);
     dev_free(ctx, g->poly);
     ctx->nchildren--;
     delete g;
@@ -650,7 +648,6 @@ tp_status tp_clover_create(tp_gauge g, double c_s, double c_t, tp_clover* out) {
       double sig[6][2][2][2][2];
       clover_sigma_table(c_s, c_t, sig);
       launch_clover_build(ctx, c, sig);
-      launch_to_half(ctx, c->a3_f, c->a3_h, int64_t(cb));
       HIP_CHECK(hipStreamSynchronize(ctx->stream));
     } catch (...) {
       tp_clover_destroy(c);

@@ -182,9 +182,9 @@ __global__ void k_wline(const double2* __restrict__ canon, double2* wd, double2*
 
 // Axial-gauge links U^ax_mu(x) = W(x)^dag U'_mu(x) W(x+mu) with Omega = W^dag (Sec. II.C,
 // App. C): every time link becomes the identity except U^ax_t(Lt-1) = W(0) = P.
-// Writes the p3 layout (F64, F32) and a canonical copy for the clover build.
+// Writes the p3 layout (F64, F32).
 __global__ void k_axial_links(const double2* __restrict__ canon, const double2* __restrict__ wd,
-                              double2* u3d, float2* u3f, double2* canon_ax, Geom g, int64_t V,
+                              double2* u3d, float2* u3f, Geom g, int64_t V,
                               double b, int* flags) {
   int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int mu = blockIdx.y;
@@ -242,11 +242,9 @@ __global__ void k_axial_links(const double2* __restrict__ canon, const double2* 
   }
   double2* d3 = u3d + ((int64_t)(mu * 2 + pa) * 9) * V2 + ia;
   float2* f3 = u3f + ((int64_t)(mu * 2 + pa) * 9) * V2;
-  double2* ca = canon_ax + ((int64_t)mu * V + n) * 9;
   for (int k = 0; k < 9; ++k) {
     d3[(int64_t)k * V2] = make_double2(T2[k].re, T2[k].im);
     f3[comp_off<float2>(k, 9, V2, ia)] = make_float2(float(T2[k].re), float(T2[k].im));
-    ca[k] = make_double2(T2[k].re, T2[k].im);
   }
 }
 
@@ -325,6 +323,25 @@ struct SigTab {
   double2 s[6][2][2][2];  // plane, chirality, row, col:  coef_p * V_chi^dag sigma_p V_chi / 2
 };
 
+// U_mu(x) from the planes [4 dir][2 parity][9][V2] of a layout: p3 (the axial frame) when AX,
+// else p4 (the original frame).  The phase b folded into U_t(Lt-1) cancels in closed loops.
+template <bool AX>
+TP_DEV void load_soa(const double2* __restrict__ u, const Geom& g, int mu, int x, int y, int z, int t,
+                     cx<double>* m) {
+  x = x < 0 ? x + g.Lx : (x >= g.Lx ? x - g.Lx : x);
+  y = y < 0 ? y + g.Ly : (y >= g.Ly ? y - g.Ly : y);
+  z = z < 0 ? z + g.Lz : (z >= g.Lz ? z - g.Lz : z);
+  t = t < 0 ? t + g.Lt : (t >= g.Lt ? t - g.Lt : t);
+  const int s = p3_index(g, x, y, z), p = AX ? (x + y + z) & 1 : (x + y + z + t) & 1;
+  const int64_t i = AX ? p3_idx(g, t, s) : s + (int64_t)g.Vs2 * t;
+  const double2* src = u + (int64_t)(mu * 2 + p) * 9 * g.V2 + i;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const double2 e = src[(int64_t)k * g.V2];
+    m[k] = cx<double>{e.x, e.y};
+  }
+}
+
 TP_DEV void load_link(const double2* canon, const Geom& g, int64_t V, int mu, int x, int y, int z,
                       int t, cx<double>* u) {
   x = (x + g.Lx) % g.Lx;
@@ -350,98 +367,172 @@ TP_DEV void chain4(const cx<double>* a, const cx<double>* b, const cx<double>* c
   mm3(t2, d, out);
 }
 
-// F_{mu nu}(x) = (Q - Q^dag)/8 - tr/3 with Q the four leaves, all oriented mu -> nu.
-TP_DEV void field_strength(const double2* canon, const Geom& g, int64_t V, int mu, int nu, int x,
-                           int y, int z, int t, cx<double>* F) {
+// F_{mu nu}(x) = (Q - Q^dag)/8 - tr/3 with Q the four leaves, all oriented mu -> nu: exactly
+// anti-hermitian as computed (each entry is the rounded negative conjugate of its mirror).
+template <bool AX>
+TP_DEV void field_strength(const double2* __restrict__ u, const Geom& g, int mu, int nu, int x, int y, int z,
+                           int t, cx<double>* F) {
   // U_d(x + am*mu + an*nu); the offsets are formed arithmetically (a direction table indexed
   // by mu and nu would live in scratch memory)
-  auto L = [&](int d, int am, int an, cx<double>* u) {
-    load_link(canon, g, V, d, x + am * (mu == 0) + an * (nu == 0), y + am * (mu == 1) + an * (nu == 1),
-              z + am * (mu == 2) + an * (nu == 2), t + am * (mu == 3) + an * (nu == 3), u);
+  auto L = [&](int d, int am, int an, cx<double>* m) {
+    load_soa<AX>(u, g, d, x + am * (mu == 0) + an * (nu == 0), y + am * (mu == 1) + an * (nu == 1),
+            z + am * (mu == 2) + an * (nu == 2), t + am * (mu == 3) + an * (nu == 3), m);
   };
   cx<double> a[9], b[9], c[9], d[9], cd[9], dd[9], leaf[9], Q[9];
+#pragma unroll
   for (int k = 0; k < 9; ++k) Q[k] = cx<double>{0, 0};
   // leaf 1: U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
   L(mu, 0, 0, a); L(nu, 1, 0, b); L(mu, 0, 1, c); L(nu, 0, 0, d);
   dag3(c, cd); dag3(d, dd); chain4(a, b, cd, dd, leaf);
+#pragma unroll
   for (int k = 0; k < 9; ++k) Q[k] += leaf[k];
   // leaf 2: U_nu(x) U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu)
   L(nu, 0, 0, a); L(mu, -1, 1, b); L(nu, -1, 0, c); L(mu, -1, 0, d);
   { cx<double> bd[9]; dag3(b, bd); dag3(c, cd); chain4(a, bd, cd, d, leaf); }
+#pragma unroll
   for (int k = 0; k < 9; ++k) Q[k] += leaf[k];
   // leaf 3: U_mu(x-mu)^dag U_nu(x-mu-nu)^dag U_mu(x-mu-nu) U_nu(x-nu)
   L(mu, -1, 0, a); L(nu, -1, -1, b); L(mu, -1, -1, c); L(nu, 0, -1, d);
   { cx<double> ad[9], bd[9]; dag3(a, ad); dag3(b, bd); chain4(ad, bd, c, d, leaf); }
+#pragma unroll
   for (int k = 0; k < 9; ++k) Q[k] += leaf[k];
   // leaf 4: U_nu(x-nu)^dag U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^dag
   L(nu, 0, -1, a); L(mu, 0, -1, b); L(nu, 1, -1, c); L(mu, 0, 0, d);
   { cx<double> ad[9]; dag3(a, ad); dag3(d, dd); chain4(ad, b, c, dd, leaf); }
+#pragma unroll
   for (int k = 0; k < 9; ++k) Q[k] += leaf[k];
+#pragma unroll
   for (int i = 0; i < 3; ++i)
+#pragma unroll
     for (int j = 0; j < 3; ++j) F[3 * i + j] = 0.125 * (Q[3 * i + j] - conj(Q[3 * j + i]));
   cx<double> tr = (1.0 / 3.0) * (F[0] + F[4] + F[8]);
   F[0] -= tr; F[4] -= tr; F[8] -= tr;
 }
 
-// One chiral block C of the clover term at every site: the sum over the six planes of the
-// sigma-table coefficients times F_{mu nu}, accumulated only into the stored entries of the
-// hermitian 6x6 block (6 real diagonal, 15 complex below it), all at compile-time indices so
-// that they stay in registers.
+// The set-up kernels below work on sub-blocks of 16 spatial indices x 4 time slices of one p3
+// parity: 64 sites that are runs of 256 bytes both in the p4 planes (s fastest) and in the p3
+// planes (four tiles of 4 lines x 4 slices).  Workgroups go to the 8 XCDs in turn; each XCD takes
+// one contiguous part of the sequence parity, s, t (fastest first), so that a site's neighbours
+// in x, y and z were read through the same L2 at most one z plane x 4 slices (1.3 MB of links at
+// 24^2) earlier.
+constexpr int kSub = 64;
+struct SubSite {
+  int p, s, t;
+  bool ok;  // false past the lattice's ends: s and t are then those of the last valid site
+};
+unsigned sub_blocks(const Lattice& L) { return 2u * unsigned((L.Vs2 + 15) / 16) * unsigned((L.L[3] + 3) / 4); }
+TP_DEV SubSite sub_site(const Geom& g, int lane) {
+  const uint32_t n = gridDim.x, x = blockIdx.x & 7u, per = n >> 3, rest = n & 7u;
+  const uint32_t id = x * per + (x < rest ? x : rest) + (blockIdx.x >> 3);
+  const uint32_t blk = id >> 1, nsb = uint32_t(g.Vs2 + 15) / 16;
+  const int s = int(blk % nsb) * 16 + (lane & 15), t = int(blk / nsb) * 4 + (lane >> 4);
+  SubSite q;
+  q.p = int(id & 1u);
+  q.ok = s < g.Vs2 && t < g.Lt;
+  q.s = s < g.Vs2 ? s : g.Vs2 - 1;
+  q.t = t < g.Lt ? t : g.Lt - 1;
+  return q;
+}
+
+// An anti-hermitian 3x3 matrix in LDS as nine reals per site: the imaginary diagonal, then the
+// entries (1,0), (2,0), (2,1); consecutive lanes are adjacent.
+struct AntiH {
+  double* p;
+  int lane;
+  TP_DEV double& at(int k) const { return p[k * kSub + lane]; }
+  TP_DEV void put(const cx<double>* F) const {
+    at(0) = F[0].im; at(1) = F[4].im; at(2) = F[8].im;
+    at(3) = F[3].re; at(4) = F[3].im;
+    at(5) = F[6].re; at(6) = F[6].im;
+    at(7) = F[7].re; at(8) = F[7].im;
+  }
+  TP_DEV cx<double> low(int a, int b) const {  // a > b
+    const int k = a == 1 ? 3 : (b == 0 ? 5 : 7);
+    return cx<double>{at(k), at(k + 1)};
+  }
+  TP_DEV cx<double> get(int a, int b) const {
+    if (a == b) return cx<double>{0.0, at(a)};
+    if (a > b) return low(a, b);
+    const cx<double> v = low(b, a);
+    return cx<double>{-v.re, v.im};
+  }
+};
+
+// The stored entries (6 real diagonal, 15 complex below it) of chiral block C: the sum over the
+// planes of the sigma-table coefficients times F, all at compile-time indices.
 template <int C>
-__global__ void __launch_bounds__(64) k_clover_build(const double2* __restrict__ canon, double2* a3d,
-                                                     float2* a3f, double2* a4d, float2* a4f, Geom g,
-                                                     int64_t V, SigTab sig) {
-  int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= V) return;
-  int x, y, z, t;
-  canon_coords(n, g, x, y, z, t);
-  double dg[6];
-  cx<double> lo[15];
+TP_DEV void chiral_block(double* fs, int lane, const SigTab& sig, double* dg, cx<double>* lo) {
 #pragma unroll
   for (int k = 0; k < 6; ++k) dg[k] = 0.0;
 #pragma unroll
   for (int k = 0; k < 15; ++k) lo[k] = cx<double>{0, 0};
 #pragma unroll
   for (int pl = 0; pl < 6; ++pl) {
-    // planes 03 13 23 01 02 12
-    const int mu = pl < 3 ? pl : (pl == 5 ? 1 : 0);
-    const int nu = pl < 3 ? 3 : (pl == 3 ? 1 : 2);
-    const double2 w00 = sig.s[pl][C][0][0], w01 = sig.s[pl][C][0][1];
-    const double2 w10 = sig.s[pl][C][1][0], w11 = sig.s[pl][C][1][1];
-    if (fabs(w00.x) + fabs(w00.y) + fabs(w01.x) + fabs(w01.y) + fabs(w10.x) + fabs(w10.y) +
-            fabs(w11.x) + fabs(w11.y) == 0.0)
-      continue;  // coefficient zero
-    cx<double> F[9];
-    field_strength(canon, g, V, mu, nu, x, y, z, t, F);
+    const AntiH F{fs + pl * 9 * kSub, lane};
+    const double2 w00 = sig.s[pl][C][0][0], w10 = sig.s[pl][C][1][0], w11 = sig.s[pl][C][1][1];
 #pragma unroll
     for (int r = 0; r < 6; ++r)
 #pragma unroll
       for (int q = 0; q <= r; ++q) {
-        const int sr = r / 3, a = r % 3, sq = q / 3, bb = q % 3;
-        const double2 wv = sr == 0 ? (sq == 0 ? w00 : w01) : (sq == 0 ? w10 : w11);
-        const cx<double> v = cmul(cx<double>{wv.x, wv.y}, F[3 * a + bb]);
+        const int sr = r / 3, sq = q / 3;
+        const double2 wv = sr == 0 ? w00 : (sq == 0 ? w10 : w11);
+        const cx<double> v = cmul(cx<double>{wv.x, wv.y}, F.get(r % 3, q % 3));
         if (r == q) dg[r] += v.re;
         else lo[r * (r - 1) / 2 + q] += v;
       }
   }
-  int p3, p4;
-  int64_t i3, i4;
-  site_pi(g, false, x, y, z, t, p3, i3);
-  site_pi(g, true, x, y, z, t, p4, i4);
-  const int64_t V2 = V / 2;
-  double2* d3 = a3d ? a3d + ((int64_t)p3 * 36 + 18 * C) * V2 : nullptr;
-  float2* f3 = a3f ? a3f + ((int64_t)p3 * 36 + 18 * C) * V2 : nullptr;
-  double2* d4 = a4d ? a4d + ((int64_t)p4 * 36 + 18 * C) * V2 : nullptr;
-  float2* f4 = a4f ? a4f + ((int64_t)p4 * 36 + 18 * C) * V2 : nullptr;
+}
+
+// The clover term in one frame: p3 blocks from the axial-frame links (AX; every p3 operator),
+// p4 blocks from the original links (the 4D even-odd operator).  One workgroup handles 64 sites;
+// its wavefronts form F of two planes each, then, through LDS, two of them one chiral block each.
+//
+// Bound by the fabric: 72 link matrices (10 KB) per site and frame, few of which a cache still
+// holds.  F is formed once per site, not once per chirality; the links come from planes in which
+// adjacent lanes are adjacent (canonical links, 144 bytes a lane, cost one cache line per lane and
+// load), and the sub-block order keeps a neighbour's links in the XCD's L2.  Both frames at
+// 24^3x128: 6.5 ms with a thread per site, chirality and frame on canonical links; 6.4 ms in
+// blocks dealt to the XCDs in turn (20.9 GB fetched per launch); 3.6 ms so (2, 3 and 6 wavefronts
+// per workgroup: 3.7, 3.6 and 4.2 ms).
+constexpr int kClovWaves = 3;
+template <bool AX, int NW>
+__global__ void __launch_bounds__(64 * NW) k_clover_build(const double2* __restrict__ u, double2* ad, float2* af,
+                                                      __half2* ah, Geom g, SigTab sig, uint32_t planes) {
+  __shared__ double fs[6 * 9 * kSub];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const SubSite q = sub_site(g, lane);
+  const C3 c = p3_coords(g, q.p, q.s);
+#pragma unroll 1
+  for (int pl = (6 / NW) * wave; pl < (6 / NW) * (wave + 1); ++pl) {  // planes 03 13 23 | 01 02 12
+    const int mu = pl < 3 ? pl : (pl == 5 ? 1 : 0), nu = pl < 3 ? 3 : (pl == 3 ? 1 : 2);
+    cx<double> F[9];
+    if ((planes >> pl) & 1u) {
+      field_strength<AX>(u, g, mu, nu, c.x, c.y, c.z, q.t, F);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) F[k] = cx<double>{0, 0};
+    }
+    AntiH{fs + pl * 9 * kSub, lane}.put(F);
+  }
+  __syncthreads();
+  if (!q.ok || wave >= 2) return;
+  const int C = wave;
+  double dg[6];
+  cx<double> lo[15];
+  if (C == 0) chiral_block<0>(fs, lane, sig, dg, lo);
+  else chiral_block<1>(fs, lane, sig, dg, lo);
+  const int p = AX ? q.p : (q.p ^ (q.t & 1));
+  const int64_t off = ((int64_t)p * 36 + 18 * C) * g.V2;
+  const int64_t i = AX ? p3_idx(g, q.t, q.s) : q.s + (int64_t)g.Vs2 * q.t;
   // slots 0..2: diagonal pairs, 3..17: lower triangle row-major (the layout of store_herm6_parts)
 #pragma unroll
   for (int slot = 0; slot < 18; ++slot) {
     const double2 v = slot < 3 ? make_double2(dg[2 * slot], dg[2 * slot + 1])
                                : make_double2(lo[slot - 3].re, lo[slot - 3].im);
-    if (d3) d3[(int64_t)slot * V2 + i3] = v;
-    if (f3) f3[comp_off<float2>(slot, 18, V2, i3)] = make_float2(float(v.x), float(v.y));
-    if (d4) d4[(int64_t)slot * V2 + i4] = v;
-    if (f4) f4[comp_off<float2>(slot, 18, V2, i4)] = make_float2(float(v.x), float(v.y));
+    const float2 vf = make_float2(float(v.x), float(v.y));
+    ad[off + (int64_t)slot * g.V2 + i] = v;
+    af[off + comp_off<float2>(slot, 18, g.V2, i)] = vf;
+    if constexpr (AX) ah[off + comp_off<__half2>(slot, 18, g.V2, i)] = __float22half2_rn(vf);
   }
 }
 
@@ -854,7 +945,7 @@ void launch_to_half(tp_ctx ctx, const float2* src, __half2* dst, int64_t n) {
 void launch_axial_links(tp_ctx ctx, tp_gauge g, int* flags) {
   const Lattice& L = ctx->lat;
   hipLaunchKernelGGL(k_axial_links, dim3(nblk(L.V, 64), 4), dim3(64), 0, ctx->stream, g->canon,
-                     g->w_d, g->u3_d, g->u3_f, g->canon_ax, L.g, L.V, double(ctx->bc), flags);
+                     g->w_d, g->u3_d, g->u3_f, L.g, L.V, double(ctx->bc), flags);
   LAUNCH_CHECK();
 }
 
@@ -867,25 +958,21 @@ void launch_closure(tp_ctx ctx, tp_op op, double* cond) {
 }
 
 void launch_clover_build(tp_ctx ctx, tp_clover c, const double sig[6][2][2][2][2]) {
-  // p3 blocks from the axial-gauge links (the frame of every p3 operator), p4 blocks
-  // from the original links (the 4D even-odd baseline)
   const Lattice& L = ctx->lat;
   SigTab t;
+  uint32_t planes = 0;  // planes with a nonzero coefficient
   for (int p = 0; p < 6; ++p)
     for (int ch = 0; ch < 2; ++ch)
       for (int r = 0; r < 2; ++r)
-        for (int q = 0; q < 2; ++q) t.s[p][ch][r][q] = make_double2(sig[p][ch][r][q][0], sig[p][ch][r][q][1]);
-  hipLaunchKernelGGL(k_clover_build<0>, dim3(nblk(L.V, 64)), dim3(64), 0, ctx->stream, c->g->canon_ax,
-                     c->a3_d, c->a3_f, (double2*)nullptr, (float2*)nullptr, L.g, L.V, t);
+        for (int q = 0; q < 2; ++q) {
+          t.s[p][ch][r][q] = make_double2(sig[p][ch][r][q][0], sig[p][ch][r][q][1]);
+          if (sig[p][ch][r][q][0] != 0.0 || sig[p][ch][r][q][1] != 0.0) planes |= 1u << p;
+        }
+  hipLaunchKernelGGL((k_clover_build<true, kClovWaves>), dim3(sub_blocks(L)), dim3(64 * kClovWaves), 0, ctx->stream, c->g->u3_d, c->a3_d,
+                     c->a3_f, c->a3_h, L.g, t, planes);
   LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_clover_build<1>, dim3(nblk(L.V, 64)), dim3(64), 0, ctx->stream, c->g->canon_ax,
-                     c->a3_d, c->a3_f, (double2*)nullptr, (float2*)nullptr, L.g, L.V, t);
-  LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_clover_build<0>, dim3(nblk(L.V, 64)), dim3(64), 0, ctx->stream, c->g->canon,
-                     (double2*)nullptr, (float2*)nullptr, c->a4_d, c->a4_f, L.g, L.V, t);
-  LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_clover_build<1>, dim3(nblk(L.V, 64)), dim3(64), 0, ctx->stream, c->g->canon,
-                     (double2*)nullptr, (float2*)nullptr, c->a4_d, c->a4_f, L.g, L.V, t);
+  hipLaunchKernelGGL((k_clover_build<false, kClovWaves>), dim3(sub_blocks(L)), dim3(64 * kClovWaves), 0, ctx->stream, c->g->u4_d, c->a4_d,
+                     c->a4_f, (__half2*)nullptr, L.g, t, planes);
   LAUNCH_CHECK();
 }
 

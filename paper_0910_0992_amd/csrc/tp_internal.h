@@ -146,7 +146,6 @@ struct tp_gauge_s {
   double2* u4_d = nullptr;   // p4 layout [4 dir][2 par][9][V2], time phase folded
   float2* u4_f = nullptr;
   double2* w_d = nullptr;    // p3 layout W(t) = U(t)...U(Lt-1) [2 par][9][V2], FP64
-  double2* canon_ax = nullptr;  // axial-gauge links, canonical order (clover build)
   double2* poly = nullptr;   // W(0) per line [2 par][9][Vs2]
   // every axial-frame spatial link is SU(3) to 1e-9: FP32/FP16 kernels read two rows
   bool su3_spatial = false;

@@ -1,0 +1,47 @@
+"""Kernels at the edges of their blocks: lattices smaller than a block, and remainders in every
+extent that a block splits, against the FP64 oracle.
+
+Tolerance: FP64 results are re-expressions of the oracle's, a few hundred operations of 1.1e-16
+deep, so 1e-12 of the field's norm (as for every FP64 apply) leaves two orders of magnitude.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle.schemes import Operator as OOp
+
+pytestmark = pytest.mark.gpu
+
+TOL64 = 1e-12
+
+
+def _make(dims, xi=3.0, m0=0.05, cs=1.6, ct=1.0, bc=-1, seed=1100):
+    from paper_0910_0992_amd import Operator
+    U = synth.make_links(dims, 0.35, 0.2, seed)
+    print(f"[case] {dims}", flush=True)
+    return U, OOp(U, m0, xi, float(bc), cs / xi, ct), Operator(torch.from_numpy(U).cuda(), m0, xi, cs / xi, ct, bc)
+
+
+def _rel(a, b):
+    a = a.cpu().numpy()
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+# sub-blocks of the set-up kernels are 16 spatial indices (of one parity) x 4 slices
+SUB_DIMS = [(2, 2, 2, 2), (2, 2, 2, 5), (4, 2, 4, 4), (8, 2, 2, 3), (6, 2, 6, 9), (4, 4, 4, 16)]
+
+
+@pytest.mark.parametrize("dims", SUB_DIMS)
+@pytest.mark.parametrize("planes", ["all", "time", "space"])
+def test_clover_term(dims, planes):
+    """The clover term in the axial frame (apply_clover) and in the original one (the 4D scheme)."""
+    U, o, g = _make(dims, cs=0.0 if planes == "time" else 1.6, ct=0.0 if planes == "space" else 1.0)
+    eta = synth.make_source(dims, 2100)
+    t = torch.from_numpy(eta).cuda()
+    for plus in (0, 1, -1):
+        ref = {0: o.Aop, 1: o.Amu, -1: o.Amu_inv}[plus](eta)
+        assert _rel(g.apply_clover(t, "F64", plus), ref) < TOL64
+    if dims[3] % 2 == 0:
+        assert _rel(g.apply_prec(t, "SCHUR4D", "F64"), o.prec("SCHUR4D", eta)) < TOL64
+    g.close()
