@@ -1162,18 +1162,12 @@ tp_status tp_force(tp_op op, const void* x, const void* lambda, void* grad, int3
     need(grad, "grad_links");
     tp_ctx ctx = op->g->ctx;
     set_device(ctx);
-    Field& a = tmp_field(op, TP_F64, 0);
-    Field& b = tmp_field(op, TP_F64, 1);
-    launch_pack(ctx, static_cast<const double2*>(x), a, false, false, nullptr);
-    launch_pack(ctx, static_cast<const double2*>(lambda), b, false, false, nullptr);
     if (flags & ~(TP_FORCE_PROJECTED | TP_FORCE_HOPPING_ONLY)) TP_THROW(TP_EINVAL, "bad force flags");
-    const bool projected = (flags & TP_FORCE_PROJECTED) != 0;
-    launch_force(op, a, b, static_cast<double2*>(grad), projected);
-    if (op->c && !(flags & TP_FORCE_HOPPING_ONLY)) {
-      double sig[6][4][4][2];
-      sigma_planes(sig);
-      launch_clover_force(op, a, b, static_cast<double2*>(grad), projected, sig);
-    }
+    double sig[6][4][4][2];
+    sigma_planes(sig);
+    launch_force(op, static_cast<const double2*>(x), static_cast<const double2*>(lambda),
+                 static_cast<double2*>(grad), (flags & TP_FORCE_PROJECTED) != 0,
+                 op->c && !(flags & TP_FORCE_HOPPING_ONLY), sig);
   });
 }
 

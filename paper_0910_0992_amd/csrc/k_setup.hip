@@ -2,6 +2,7 @@
 // packing, the per-time-line products W(t) and the FP64 closure of T^-1,
 // the clover term in its chiral block form and (A + mu)^-1.
 #include "tp_internal.h"
+#include "tp_links.h"
 
 namespace {
 
@@ -133,18 +134,6 @@ __global__ void k_pack_links4(const double2* __restrict__ canon, double2* u4d, f
     d4[(int64_t)k * V2] = e;
     f4[comp_off<float2>(k, 9, V2, i4)] = make_float2(float(e.x), float(e.y));
   }
-}
-
-TP_DEV void mm3(const cx<double>* a, const cx<double>* b, cx<double>* c) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cx<double> s = cmul(a[3 * i], b[j]);
-      s += cmul(a[3 * i + 1], b[3 + j]);
-      s += cmul(a[3 * i + 2], b[6 + j]);
-      c[3 * i + j] = s;
-    }
 }
 
 // W(t) = U'(t) U'(t+1) ... U'(Lt-1) per time line, U' the time links with the phase b
@@ -323,25 +312,6 @@ struct SigTab {
   double2 s[6][2][2][2];  // plane, chirality, row, col:  coef_p * V_chi^dag sigma_p V_chi / 2
 };
 
-// U_mu(x) from the planes [4 dir][2 parity][9][V2] of a layout: p3 (the axial frame) when AX,
-// else p4 (the original frame).  The phase b folded into U_t(Lt-1) cancels in closed loops.
-template <bool AX>
-TP_DEV void load_soa(const double2* __restrict__ u, const Geom& g, int mu, int x, int y, int z, int t,
-                     cx<double>* m) {
-  x = x < 0 ? x + g.Lx : (x >= g.Lx ? x - g.Lx : x);
-  y = y < 0 ? y + g.Ly : (y >= g.Ly ? y - g.Ly : y);
-  z = z < 0 ? z + g.Lz : (z >= g.Lz ? z - g.Lz : z);
-  t = t < 0 ? t + g.Lt : (t >= g.Lt ? t - g.Lt : t);
-  const int s = p3_index(g, x, y, z), p = AX ? (x + y + z) & 1 : (x + y + z + t) & 1;
-  const int64_t i = AX ? p3_idx(g, t, s) : s + (int64_t)g.Vs2 * t;
-  const double2* src = u + (int64_t)(mu * 2 + p) * 9 * g.V2 + i;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    const double2 e = src[(int64_t)k * g.V2];
-    m[k] = cx<double>{e.x, e.y};
-  }
-}
-
 TP_DEV void load_link(const double2* canon, const Geom& g, int64_t V, int mu, int x, int y, int z,
                       int t, cx<double>* u) {
   x = (x + g.Lx) % g.Lx;
@@ -352,12 +322,6 @@ TP_DEV void load_link(const double2* canon, const Geom& g, int64_t V, int mu, in
   const double2* src = canon + ((int64_t)mu * V + n) * 9;
 #pragma unroll
   for (int k = 0; k < 9; ++k) u[k] = cx<double>{src[k].x, src[k].y};
-}
-TP_DEV void dag3(const cx<double>* a, cx<double>* b) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) b[3 * i + j] = conj(a[3 * j + i]);
 }
 TP_DEV void chain4(const cx<double>* a, const cx<double>* b, const cx<double>* c,
                    const cx<double>* d, cx<double>* out) {
@@ -407,31 +371,6 @@ TP_DEV void field_strength(const double2* __restrict__ u, const Geom& g, int mu,
     for (int j = 0; j < 3; ++j) F[3 * i + j] = 0.125 * (Q[3 * i + j] - conj(Q[3 * j + i]));
   cx<double> tr = (1.0 / 3.0) * (F[0] + F[4] + F[8]);
   F[0] -= tr; F[4] -= tr; F[8] -= tr;
-}
-
-// The set-up kernels below work on sub-blocks of 16 spatial indices x 4 time slices of one p3
-// parity: 64 sites that are runs of 256 bytes both in the p4 planes (s fastest) and in the p3
-// planes (four tiles of 4 lines x 4 slices).  Workgroups go to the 8 XCDs in turn; each XCD takes
-// one contiguous part of the sequence parity, s, t (fastest first), so that a site's neighbours
-// in x, y and z were read through the same L2 at most one z plane x 4 slices (1.3 MB of links at
-// 24^2) earlier.
-constexpr int kSub = 64;
-struct SubSite {
-  int p, s, t;
-  bool ok;  // false past the lattice's ends: s and t are then those of the last valid site
-};
-unsigned sub_blocks(const Lattice& L) { return 2u * unsigned((L.Vs2 + 15) / 16) * unsigned((L.L[3] + 3) / 4); }
-TP_DEV SubSite sub_site(const Geom& g, int lane) {
-  const uint32_t n = gridDim.x, x = blockIdx.x & 7u, per = n >> 3, rest = n & 7u;
-  const uint32_t id = x * per + (x < rest ? x : rest) + (blockIdx.x >> 3);
-  const uint32_t blk = id >> 1, nsb = uint32_t(g.Vs2 + 15) / 16;
-  const int s = int(blk % nsb) * 16 + (lane & 15), t = int(blk / nsb) * 4 + (lane >> 4);
-  SubSite q;
-  q.p = int(id & 1u);
-  q.ok = s < g.Vs2 && t < g.Lt;
-  q.s = s < g.Vs2 ? s : g.Vs2 - 1;
-  q.t = t < g.Lt ? t : g.Lt - 1;
-  return q;
 }
 
 // An anti-hermitian 3x3 matrix in LDS as nine reals per site: the imaginary diagonal, then the
@@ -723,184 +662,6 @@ void unpack_t(tp_ctx ctx, const Field& src, double2* canon, bool l4, bool g5, co
 }
 
 
-// ---- SW-term link force -----------------------------------------------------------------
-// With x and lambda (dL = -Re <lambda, dM x>), the SW term contributes
-//   s(U) = Re sum_x sum_p tr(Q_p(x) Yh_p(x)),  Yh_p = (c_p/2)(Z - Z^dag),
-//   Z = W/8 - tr(W)/24,  W_p(x) = sum_{s s'} sigma_p[s][s'] x_s'(x) lambda_s(x)^dag,
-// Q_p the four-leaf sum of plane p.  Each leaf is a plaquette read from one of its corners,
-// so a link's derivative collects, from each plaquette that contains it, the product of the
-// other three factors with Yh of every corner inserted at that corner.
-struct SigmaTab {
-  double2 s[6][4][4];  // sigma_{mu nu} = [gamma_mu, gamma_nu]/2, planes (03 13 23 01 02 12)
-};
-
-TP_DEV int plane_index(int a, int b) {  // a < b
-  return b == 3 ? a : (a == 0 ? (b == 1 ? 3 : 4) : 5);
-}
-
-__global__ void __launch_bounds__(128) k_clover_Y(SpinorF<double2> x0, SpinorF<double2> x1,
-                                                   SpinorF<double2> l0, SpinorF<double2> l1,
-                                                   double2* Y, Geom g, int64_t V, SigmaTab sig,
-                                                   double c_s, double c_t) {
-  int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= V) return;
-  int x, y, z, t;
-  canon_coords(n, g, x, y, z, t);
-  const int p = (x + y + z) & 1;
-  const int64_t i = p3_idx(g, t, (x + g.Lx * (y + g.Ly * z)) >> 1);
-  cx<double> xs[12], ls[12];
-  load_spinor<double2, double>(p ? x1 : x0, i, xs);
-  load_spinor<double2, double>(p ? l1 : l0, i, ls);
-  // W_ba = sum_s v_sb conj(lambda_sa) with v_sb = sum_s' sigma_ss' x_s'b; every loop is
-  // unrolled so that the spinor components and the table are read at constant indices (arrays
-  // indexed by a loop variable would live in scratch memory)
-#pragma unroll
-  for (int pl = 0; pl < 6; ++pl) {
-    cx<double> W[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) W[k] = czero<double>();
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      cx<double> v[3] = {czero<double>(), czero<double>(), czero<double>()};
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp) {
-        const cx<double> sg = cx<double>{sig.s[pl][s][sp].x, sig.s[pl][s][sp].y};
-#pragma unroll
-        for (int b = 0; b < 3; ++b) v[b] += cmul(sg, xs[3 * sp + b]);
-      }
-#pragma unroll
-      for (int b = 0; b < 3; ++b)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) W[3 * b + a] += cmul(v[b], conj(ls[3 * s + a]));
-    }
-    const cx<double> tr = W[0] + W[4] + W[8];
-    const double c = 0.5 * (pl < 3 ? c_t : c_s);
-    double2* out = Y + ((int64_t)pl * V + n) * 9;
-    for (int r = 0; r < 3; ++r)
-      for (int q = 0; q < 3; ++q) {
-        cx<double> zrq = (1.0 / 8.0) * W[3 * r + q], zqr = (1.0 / 8.0) * W[3 * q + r];
-        if (r == q) {
-          zrq -= (1.0 / 24.0) * tr;
-          zqr -= (1.0 / 24.0) * tr;
-        }
-        const cx<double> v = c * (zrq - conj(zqr));
-        out[3 * r + q] = make_double2(v.re, v.im);
-      }
-  }
-}
-
-TP_DEV void load_y(const double2* Y, const Geom& g, int64_t V, int pl, int x, int y, int z, int t,
-                   cx<double>* m) {
-  x = (x + g.Lx) % g.Lx;
-  y = (y + g.Ly) % g.Ly;
-  z = (z + g.Lz) % g.Lz;
-  t = (t + g.Lt) % g.Lt;
-  const int64_t n = (int64_t)x + (int64_t)g.Lx * (y + (int64_t)g.Ly * (z + (int64_t)g.Lz * t));
-  const double2* src = Y + ((int64_t)pl * V + n) * 9;
-  for (int k = 0; k < 9; ++k) m[k] = cx<double>{src[k].x, src[k].y};
-}
-
-TP_DEV void madd3(const cx<double>* a, const cx<double>* b, cx<double>* acc) {
-  cx<double> c[9];
-  mm3(a, b, c);
-  for (int k = 0; k < 9; ++k) acc[k] += c[k];
-}
-
-// R = Ya M1 M2 M3 + M1 Yb M2 M3 + M1 M2 Yc M3 + M1 M2 M3 Yd
-TP_DEV void insert4(const cx<double>* M1, const cx<double>* M2, const cx<double>* M3, const cx<double>* Ya,
-                    const cx<double>* Yb, const cx<double>* Yc, const cx<double>* Yd, cx<double>* R) {
-  cx<double> P23[9], P123[9], T[9], P12[9];
-  mm3(M2, M3, P23);
-  mm3(M1, P23, P123);
-  mm3(Ya, P123, R);
-  mm3(Yb, P23, T);
-  madd3(M1, T, R);
-  mm3(M1, M2, P12);
-  mm3(Yc, M3, T);
-  madd3(P12, T, R);
-  madd3(P123, Yd, R);
-}
-
-__global__ void __launch_bounds__(64) k_clover_force(const double2* __restrict__ canon,
-                                                      const double2* __restrict__ Y, double2* grad,
-                                                      Geom g, int64_t V, int projected) {
-  int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int mu = blockIdx.y;
-  if (n >= V) return;
-  int c[4];
-  canon_coords(n, g, c[0], c[1], c[2], c[3]);
-  auto at = [&](int d1, int s1, int d2, int s2, int& X, int& Yy, int& Z, int& T) {
-    int q[4] = {c[0], c[1], c[2], c[3]};
-    if (d1 >= 0) q[d1] += s1;
-    if (d2 >= 0) q[d2] += s2;
-    X = q[0]; Yy = q[1]; Z = q[2]; T = q[3];
-  };
-  cx<double> G[9];
-  for (int k = 0; k < 9; ++k) G[k] = czero<double>();
-  for (int nu = 0; nu < 4; ++nu) {
-    if (nu == mu) continue;
-    const int a = mu < nu ? mu : nu, b = mu < nu ? nu : mu;
-    const int pl = plane_index(a, b);
-    cx<double> L0[9], L1[9], L2[9], L3[9], T[9], Ya[9], Yb[9], Yc[9], Yd[9], R[9];
-    int X, Yy, Z, Tt;
-    // plaquette(base): L0 = U_a(base), L1 = U_b(base+a), L2 = U_a(base+b)^dag, L3 = U_b(base)^dag
-    // corners c0 = base, c1 = base+a, c2 = base+a+b, c3 = base+b
-    auto load_plaq = [&](int d, int sd) {  // base = x + sd * e_d (d < 0: base = x)
-      at(d, sd, -1, 0, X, Yy, Z, Tt);
-      const int bx = X, by = Yy, bz = Z, bt = Tt;
-      int e[4][4] = {{1, 0, 0, 0}, {0, 1, 0, 0}, {0, 0, 1, 0}, {0, 0, 0, 1}};
-      load_link(canon, g, V, a, bx, by, bz, bt, L0);
-      load_link(canon, g, V, b, bx + e[a][0], by + e[a][1], bz + e[a][2], bt + e[a][3], L1);
-      load_link(canon, g, V, a, bx + e[b][0], by + e[b][1], bz + e[b][2], bt + e[b][3], T);
-      dag3(T, L2);
-      load_link(canon, g, V, b, bx, by, bz, bt, T);
-      dag3(T, L3);
-      load_y(Y, g, V, pl, bx, by, bz, bt, Ya);                                              // c0
-      load_y(Y, g, V, pl, bx + e[a][0], by + e[a][1], bz + e[a][2], bt + e[a][3], Yb);      // c1
-      load_y(Y, g, V, pl, bx + e[a][0] + e[b][0], by + e[a][1] + e[b][1], bz + e[a][2] + e[b][2],
-             bt + e[a][3] + e[b][3], Yc);                                                   // c2
-      load_y(Y, g, V, pl, bx + e[b][0], by + e[b][1], bz + e[b][2], bt + e[b][3], Yd);      // c3
-    };
-    if (mu == a) {
-      // the link is L0 of the plaquette based at x, and L2 (daggered) of the one at x - b
-      load_plaq(-1, 0);
-      insert4(L1, L2, L3, Yb, Yc, Yd, Ya, R);  // R_0: corners c1 c2 c3 before L1 L2 L3, c0 last
-      dag3(R, T);
-      for (int k = 0; k < 9; ++k) G[k] += T[k];
-      load_plaq(b, -1);
-      insert4(L3, L0, L1, Yd, Ya, Yb, Yc, R);  // R_2
-      for (int k = 0; k < 9; ++k) G[k] += R[k];
-    } else {
-      // the link is L1 of the plaquette based at x - a, and L3 (daggered) of the one at x
-      load_plaq(a, -1);
-      insert4(L2, L3, L0, Yc, Yd, Ya, Yb, R);  // R_1
-      dag3(R, T);
-      for (int k = 0; k < 9; ++k) G[k] += T[k];
-      load_plaq(-1, 0);
-      insert4(L0, L1, L2, Ya, Yb, Yc, Yd, R);  // R_3
-      for (int k = 0; k < 9; ++k) G[k] += R[k];
-    }
-  }
-  double2* out = grad + ((int64_t)mu * V + n) * 9;
-  if (!projected) {
-    for (int k = 0; k < 9; ++k) out[k] = make_double2(out[k].x + G[k].re, out[k].y + G[k].im);
-    return;
-  }
-  // su(3) projection TH[i U G^dag]
-  cx<double> U[9], Gd[9], M[9];
-  load_link(canon, g, V, mu, c[0], c[1], c[2], c[3], U);
-  dag3(G, Gd);
-  mm3(U, Gd, M);
-  for (int k = 0; k < 9; ++k) M[k] = cx<double>{-M[k].im, M[k].re};  // i U G^dag
-  const double trh = (M[0].re + M[4].re + M[8].re) / 3.0;
-  for (int r = 0; r < 3; ++r)
-    for (int q = 0; q < 3; ++q) {
-      cx<double> h = 0.5 * (M[3 * r + q] + conj(M[3 * q + r]));
-      if (r == q) h.re -= trh;
-      out[3 * r + q] = make_double2(out[3 * r + q].x + h.re, out[3 * r + q].y + h.im);
-    }
-}
-
 }  // namespace
 
 void launch_pack(tp_ctx ctx, const double2* canon, Field& dst, bool l4, bool g5, const double2* w) {
@@ -993,29 +754,4 @@ void launch_plaquette(tp_ctx ctx, tp_gauge g, double* part) {
   hipLaunchKernelGGL(k_plaquette, dim3(nblk(L.V)), dim3(kBlock), 0, ctx->stream, g->canon, L.g,
                      L.V, part);
   LAUNCH_CHECK();
-}
-
-void launch_clover_force(tp_op op, const Field& x, const Field& lam, double2* grad, bool projected,
-                         const double sig[6][4][4][2]) {
-  tp_ctx ctx = op->g->ctx;
-  const Lattice& L = ctx->lat;
-  SigmaTab t;
-  for (int p = 0; p < 6; ++p)
-    for (int r = 0; r < 4; ++r)
-      for (int q = 0; q < 4; ++q) t.s[p][r][q] = make_double2(sig[p][r][q][0], sig[p][r][q][1]);
-  double2* Y = static_cast<double2*>(dev_alloc(ctx, size_t(6) * L.V * 9 * sizeof(double2)));
-  try {
-    hipLaunchKernelGGL(k_clover_Y, dim3(nblk(L.V, 128)), dim3(128), 0, ctx->stream, x.par<double2>(0),
-                       x.par<double2>(1), lam.par<double2>(0), lam.par<double2>(1), Y, L.g, L.V, t,
-                       op->c->cs, op->c->ct);
-    LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_clover_force, dim3(nblk(L.V, 64), 4), dim3(64), 0, ctx->stream, op->g->canon, Y,
-                       grad, L.g, L.V, projected ? 1 : 0);
-    LAUNCH_CHECK();
-    HIP_CHECK(hipStreamSynchronize(ctx->stream));
-  } catch (...) {
-    dev_free(ctx, Y);
-    throw;
-  }
-  dev_free(ctx, Y);
 }

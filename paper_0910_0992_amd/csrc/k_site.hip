@@ -1,7 +1,6 @@
 // Site-parallel stencil kernels: the fermion matrix and its pieces on the p3
-// ("line") layout, the 4D even-odd Schur pieces on the p4 layout, and the
-// link-gradient kernel.  One thread per output site; spin projection in the
-// Dirac-Pauli basis (only two colour matvecs per hop direction).
+// ("line") layout and the 4D even-odd Schur pieces on the p4 layout.  One thread per output
+// site; spin projection in the Dirac-Pauli basis (only two colour matvecs per hop direction).
 #include <type_traits>
 
 #include "tp_internal.h"
@@ -175,124 +174,6 @@ __global__ void __launch_bounds__(kBlock) k_schur4d(ArgsP4<S> a) {
     store_spinor<S, R>(a.dst, i, w);
   } else {
     store_spinor<S, R>(a.dst, i, v);
-  }
-}
-
-// ---- link gradient ----------------------------------------------------------------------------
-// Per link U_mu(s):  K = Y + Z^dag with
-//   Y_ca = sum_a [P-^mu x(s+mu)]_{a c} conj(lambda(s)_{a a'}),
-//   Z_ca = sum_a [P+^mu x(s)]_{a c} conj(lambda(s+mu)_{a a'});
-// raw gradient k b K^dag, projected k b TH(i U K).
-TP_DEV void proj_full(int mu, bool minus, const cx<double>* x, cx<double>* out) {
-  // out = (1 -+ gamma_mu)/2 x, as a full 4-spinor
-  if (mu == 3) {
-    for (int c = 0; c < 12; ++c) out[c] = czero<double>();
-    int off = minus ? 6 : 0;
-    for (int c = 0; c < 6; ++c) out[off + c] = x[off + c];
-    return;
-  }
-  cx<double> h[6], a[3], b[3];
-  double sg = minus ? 1.0 : -1.0;  // h = x_up + sg * i s_k x_lo
-  if (mu == 0) is_k<0, double>(x + 6, x + 9, a, b);
-  else if (mu == 1) is_k<1, double>(x + 6, x + 9, a, b);
-  else is_k<2, double>(x + 6, x + 9, a, b);
-  for (int c = 0; c < 3; ++c) { h[c] = x[c] + sg * a[c]; h[3 + c] = x[3 + c] + sg * b[c]; }
-  if (mu == 0) is_k<0, double>(h, h + 3, a, b);
-  else if (mu == 1) is_k<1, double>(h, h + 3, a, b);
-  else is_k<2, double>(h, h + 3, a, b);
-  // lower = -sg * i s_k h
-  for (int c = 0; c < 3; ++c) {
-    out[c] = 0.5 * h[c];
-    out[3 + c] = 0.5 * h[3 + c];
-    out[6 + c] = (-0.5 * sg) * a[c];
-    out[9 + c] = (-0.5 * sg) * b[c];
-  }
-}
-
-// One direction mu (a compile-time constant, so that no array is indexed by it: such arrays
-// would live in scratch memory).
-template <int mu>
-TP_DEV void force_site(SpinorF<double2> x0, SpinorF<double2> x1, SpinorF<double2> l0,
-                       SpinorF<double2> l1, const double2* __restrict__ canon, double2* grad,
-                       const Geom& g, int64_t V, double inv_gf, double b, int projected, int64_t n) {
-  int x = int(n % g.Lx);
-  int64_t r = n / g.Lx;
-  int y = int(r % g.Ly);
-  r /= g.Ly;
-  int z = int(r % g.Lz);
-  int t = int(r / g.Lz);
-  // s + mu
-  const int xn = mu == 0 ? (x + 1 == g.Lx ? 0 : x + 1) : x;
-  const int yn = mu == 1 ? (y + 1 == g.Ly ? 0 : y + 1) : y;
-  const int zn = mu == 2 ? (z + 1 == g.Lz ? 0 : z + 1) : z;
-  const int tn = mu == 3 ? (t + 1 == g.Lt ? 0 : t + 1) : t;
-  auto p3 = [&](int X, int Y, int Z, int T, int& p, int64_t& i) {
-    p = (X + Y + Z) & 1;
-    i = p3_idx(g, T, (X + g.Lx * (Y + g.Ly * Z)) >> 1);
-  };
-  int pa, pb;
-  int64_t ia, ib;
-  p3(x, y, z, t, pa, ia);
-  p3(xn, yn, zn, tn, pb, ib);
-  cx<double> xa[12], xb[12], la[12], lb[12], px[12];
-  load_spinor<double2, double>(pa ? x1 : x0, ia, xa);
-  load_spinor<double2, double>(pb ? x1 : x0, ib, xb);
-  load_spinor<double2, double>(pa ? l1 : l0, ia, la);
-  load_spinor<double2, double>(pb ? l1 : l0, ib, lb);
-  cx<double> K[9];
-  for (int k = 0; k < 9; ++k) K[k] = czero<double>();
-  proj_full(mu, true, xb, px);  // P- x(s+mu)
-  for (int c = 0; c < 3; ++c)
-    for (int a = 0; a < 3; ++a) {
-      cx<double> s = czero<double>();
-      for (int al = 0; al < 4; ++al) s += cmulc(la[3 * al + a], px[3 * al + c]);
-      K[3 * c + a] += s;  // Y_ca
-    }
-  proj_full(mu, false, xa, px);  // P+ x(s)
-  for (int c = 0; c < 3; ++c)
-    for (int a = 0; a < 3; ++a) {
-      cx<double> s = czero<double>();
-      for (int al = 0; al < 4; ++al) s += cmulc(lb[3 * al + a], px[3 * al + c]);
-      K[3 * a + c] += conj(s);  // (Z^dag)_ac = conj(Z_ca)
-    }
-  double fac = (mu == 3 ? 1.0 : inv_gf) * ((mu == 3 && t == g.Lt - 1) ? b : 1.0);
-  double2* out = grad + ((int64_t)mu * V + n) * 9;
-  if (!projected) {
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) {
-        cx<double> v = fac * conj(K[3 * j + i]);
-        out[3 * i + j] = make_double2(v.re, v.im);
-      }
-    return;
-  }
-  const double2* u = canon + ((int64_t)mu * V + n) * 9;
-  cx<double> U[9], M[9];
-  for (int k = 0; k < 9; ++k) U[k] = cx<double>{u[k].x, u[k].y};
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      cx<double> s = czero<double>();
-      for (int k = 0; k < 3; ++k) s += cmul(U[3 * i + k], K[3 * k + j]);
-      M[3 * i + j] = ti(s);  // i U K
-    }
-  double tr = (M[0].re + M[4].re + M[8].re) / 3.0;  // tr of (M + M^dag)/2 over 3
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      cx<double> h = 0.5 * (M[3 * i + j] + conj(M[3 * j + i]));
-      if (i == j) h.re -= tr;
-      out[3 * i + j] = make_double2(fac * h.re, fac * h.im);
-    }
-}
-
-__global__ void __launch_bounds__(128) k_force(SpinorF<double2> x0, SpinorF<double2> x1, SpinorF<double2> l0,
-                        SpinorF<double2> l1, const double2* __restrict__ canon, double2* grad,
-                        Geom g, int64_t V, double inv_gf, double b, int projected) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= V) return;
-  switch (blockIdx.y) {
-    case 0: force_site<0>(x0, x1, l0, l1, canon, grad, g, V, inv_gf, b, projected, n); break;
-    case 1: force_site<1>(x0, x1, l0, l1, canon, grad, g, V, inv_gf, b, projected, n); break;
-    case 2: force_site<2>(x0, x1, l0, l1, canon, grad, g, V, inv_gf, b, projected, n); break;
-    default: force_site<3>(x0, x1, l0, l1, canon, grad, g, V, inv_gf, b, projected, n); break;
   }
 }
 
@@ -522,14 +403,4 @@ void launch_schur4d(tp_op op, int prec, int mode, int p, const Field* src, Field
     case TP_F64: schur4d_t<double2>(op, mode, p, src, dst, in2, c_h, c_in, ck); break;
     default: schur4d_t<float2>(op, mode, p, src, dst, in2, c_h, c_in, ck); break;
   }
-}
-
-void launch_force(tp_op op, const Field& x, const Field& lam, double2* grad, bool projected) {
-  tp_ctx ctx = op->g->ctx;
-  const Lattice& L = ctx->lat;
-  ProfScope ps(ctx, KID_FORCE, double(L.V) * 4 * (4 * 192 + 144 + 144));
-  hipLaunchKernelGGL(k_force, dim3((unsigned)((L.V + 127) / 128), 4), dim3(128), 0, ctx->stream,
-                     x.par<double2>(0), x.par<double2>(1), lam.par<double2>(0), lam.par<double2>(1),
-                     op->g->canon, grad, L.g, L.V, 1.0 / op->gf, double(ctx->bc), projected ? 1 : 0);
-  LAUNCH_CHECK();
 }

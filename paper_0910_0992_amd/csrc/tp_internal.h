@@ -384,10 +384,11 @@ void bicg_state(tp_ctx ctx, double* out);
 double finish_norm(tp_ctx ctx, int nblocks);
 
 // ---------------------------------------------------------------- force
-// SW-term part of the link gradient (added to grad), sig = sigma_{mu nu} of planes 03 13 23 01 02 12
-void launch_clover_force(tp_op op, const Field& x, const Field& lam, double2* grad, bool projected,
-                         const double sig[6][4][4][2]);
-void launch_force(tp_op op, const Field& x, const Field& lam, double2* grad, bool projected);
+// Link gradient from canonical x and lambda; with `clover` the SW term's part is included, sig =
+// sigma_{mu nu} of planes 03 13 23 01 02 12 (k_force.hip).
+void launch_force(tp_op op, const double2* x, const double2* lam, double2* grad, bool projected, bool clover,
+                  const double sig[6][4][4][2]);
+constexpr int W_FORCE = 110;  // first of its five FP64 work fields
 
 // ---------------------------------------------------------------- composite operators (ops.cpp)
 void op_apply_M(tp_op op, int prec, const Field& src, Field& dst, bool dagger);

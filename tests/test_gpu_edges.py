@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import synth
+from oracle import force as oforce
 from oracle.schemes import Operator as OOp
 
 pytestmark = pytest.mark.gpu
@@ -44,4 +45,17 @@ def test_clover_term(dims, planes):
         assert _rel(g.apply_clover(t, "F64", plus), ref) < TOL64
     if dims[3] % 2 == 0:
         assert _rel(g.apply_prec(t, "SCHUR4D", "F64"), o.prec("SCHUR4D", eta)) < TOL64
+    g.close()
+
+
+@pytest.mark.parametrize("dims", SUB_DIMS)
+@pytest.mark.parametrize("bc", [-1, 1])
+def test_link_gradient(dims, bc):
+    """Raw and projected link gradient, with and without the SW term's part."""
+    U, o, g = _make(dims, bc=bc)
+    x, lam = synth.make_source(dims, 2101), synth.make_source(dims, 2102)
+    tx, tl = torch.from_numpy(x).cuda(), torch.from_numpy(lam).cuda()
+    for (raw, proj), only in ((oforce.link_gradient(o, x, lam), True), (oforce.full_link_gradient(o, x, lam), False)):
+        assert _rel(g.force(tx, tl, projected=False, hopping_only=only), raw) < TOL64
+        assert _rel(g.force(tx, tl, projected=True, hopping_only=only), proj) < TOL64
     g.close()
