@@ -537,10 +537,6 @@ tp_status tp_gauge_create(tp_ctx ctx, const void* links, int32_t where, tp_gauge
     ctx->nchildren++;
     try {
       size_t lb = size_t(4) * L.V * 9 * sizeof(double2);
-      g->canon = static_cast<double2*>(dev_alloc(ctx, lb));
-      HIP_CHECK(hipMemcpyAsync(g->canon, links, lb,
-                               where == TP_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                               ctx->stream));
       g->u3_d = static_cast<double2*>(dev_alloc(ctx, lb));
       g->u3_f = static_cast<float2*>(dev_alloc(ctx, lb / 2));
       g->u3_h = static_cast<__half2*>(dev_alloc(ctx, lb / 4));
@@ -548,20 +544,28 @@ tp_status tp_gauge_create(tp_ctx ctx, const void* links, int32_t where, tp_gauge
       g->u4_f = static_cast<float2*>(dev_alloc(ctx, lb / 2));
       g->w_d = static_cast<double2*>(dev_alloc(ctx, size_t(2) * 9 * L.V2 * sizeof(double2)));
       g->poly = static_cast<double2*>(dev_alloc(ctx, size_t(2) * 9 * L.Vs2 * sizeof(double2)));
-      int* flags = static_cast<int*>(dev_alloc(ctx, 4 * sizeof(int)));
+      int* flags = nullptr;
+      double2* staged = nullptr;  // device copy of host links while they are converted
       int hf[4] = {1, 1, 1, 1};
       try {
+        flags = static_cast<int*>(dev_alloc(ctx, 4 * sizeof(int)));
+        const double2* dl = static_cast<const double2*>(links);
+        if (where == TP_HOST) {
+          staged = static_cast<double2*>(dev_alloc(ctx, lb));
+          HIP_CHECK(hipMemcpyAsync(staged, links, lb, hipMemcpyHostToDevice, ctx->stream));
+          dl = staged;
+        }
         HIP_CHECK(hipMemsetAsync(flags, 0, 4 * sizeof(int), ctx->stream));
-        launch_wline(ctx, g);
-        launch_axial_links(ctx, g, flags);
-        launch_to_half(ctx, g->u3_f, g->u3_h, int64_t(lb / sizeof(double2)));
-        launch_pack_links(ctx, g);
+        launch_wline(ctx, g, dl);
+        launch_links(ctx, g, dl, flags);
         HIP_CHECK(hipMemcpyAsync(hf, flags, 4 * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
         HIP_CHECK(hipStreamSynchronize(ctx->stream));
       } catch (...) {
+        dev_free(ctx, staged);
         dev_free(ctx, flags);
         throw;
       }
+      dev_free(ctx, staged);
       dev_free(ctx, flags);
       if (hf[2]) TP_THROW(TP_EINVAL, "links contain NaN or Inf");
       if (hf[1]) TP_THROW(TP_EINVAL, "time links must be unitary (U U^dag = 1 to 1e-10)");
@@ -581,7 +585,6 @@ tp_status tp_gauge_destroy(tp_gauge g) {
     tp_ctx ctx = g->ctx;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(g->ctx->stream);
-    dev_free(ctx, g->canon);
     dev_free(ctx, g->u3_d);
     dev_free(ctx, g->u3_f);
     dev_free(ctx, g->u3_h);
@@ -602,26 +605,20 @@ tp_status tp_gauge_plaquette(tp_gauge g, double* ps, double* pt) {
     tp_ctx ctx = g->ctx;
     set_device(ctx);
     const Lattice& L = ctx->lat;
-    int64_t nb = (L.V + 255) / 256;
-    double* part = static_cast<double*>(dev_alloc(ctx, sizeof(double) * 2 * nb));
-    std::vector<double> h(2 * nb);
+    const int64_t nb = plaquette_partials(ctx);
+    double* part = static_cast<double*>(dev_alloc(ctx, sizeof(double) * 2 * (nb + 1)));
+    double h[2];
     try {
       launch_plaquette(ctx, g, part);
-      HIP_CHECK(hipMemcpyAsync(h.data(), part, sizeof(double) * 2 * nb, hipMemcpyDeviceToHost,
-                               ctx->stream));
+      HIP_CHECK(hipMemcpyAsync(h, part + 2 * nb, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
       HIP_CHECK(hipStreamSynchronize(ctx->stream));
     } catch (...) {
       dev_free(ctx, part);
       throw;
     }
     dev_free(ctx, part);
-    double s = 0, t = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-      s += h[2 * b];
-      t += h[2 * b + 1];
-    }
-    *ps = s / (3.0 * L.V);
-    *pt = t / (3.0 * L.V);
+    *ps = h[0] / (3.0 * L.V);
+    *pt = h[1] / (3.0 * L.V);
   });
 }
 
@@ -720,8 +717,6 @@ tp_status tp_op_create(tp_gauge g, tp_clover c, double m0, double gamma_f, tp_op
       HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), ctx->stream));
       launch_closure(ctx, op, cond);
       launch_clover_derived(ctx, op, bad);
-      launch_to_half(ctx, op->a3_mu_f, op->a3_mu_h, int64_t(cb));
-      launch_to_half(ctx, op->a3_inv_f, op->a3_inv_h, int64_t(cb));
       std::vector<double> hc(2 * L.Vs2);
       int hb = 0;
       HIP_CHECK(hipMemcpyAsync(hc.data(), cond, sizeof(double) * hc.size(), hipMemcpyDeviceToHost,

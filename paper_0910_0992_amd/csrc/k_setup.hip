@@ -109,37 +109,13 @@ __global__ void k_unpack(double2* __restrict__ canon, SpinorF<S> f0, SpinorF<S> 
   for (int c = 0; c < 12; ++c) dst[c] = make_double2(d[c].re, d[c].im);
 }
 
-// links: canon [4][V][9] -> p4 FP64/FP32 (the 4D even-odd baseline), phase b folded
-// into U_t(Lt-1)
-__global__ void k_pack_links4(const double2* __restrict__ canon, double2* u4d, float2* u4f, Geom g,
-                              int64_t V, double b) {
-  int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int mu = blockIdx.y;
-  if (n >= V) return;
-  int x, y, z, t;
-  canon_coords(n, g, x, y, z, t);
-  double ph = (mu == 3 && t == g.Lt - 1) ? b : 1.0;
-  int p4;
-  int64_t i4;
-  site_pi(g, true, x, y, z, t, p4, i4);
-  const double2* src = canon + ((int64_t)mu * V + n) * 9;
-  int64_t V2 = V / 2;
-  double2* d4 = u4d + ((int64_t)(mu * 2 + p4) * 9) * V2 + i4;
-  float2* f4 = u4f + ((int64_t)(mu * 2 + p4) * 9) * V2;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    double2 e = src[k];
-    e.x *= ph;
-    e.y *= ph;
-    d4[(int64_t)k * V2] = e;
-    f4[comp_off<float2>(k, 9, V2, i4)] = make_float2(float(e.x), float(e.y));
-  }
-}
-
 // W(t) = U'(t) U'(t+1) ... U'(Lt-1) per time line, U' the time links with the phase b
 // folded into U'(Lt-1).  One thread per line: an Lt-step product, run once per gauge field.
-__global__ void k_wline(const double2* __restrict__ canon, double2* wd, double2* poly, Geom g,
-                        int64_t V, double b) {
+// Bound by the latency of the links' loads, which do not depend on the product: they are issued
+// kAhead slices ahead (24^3x128: 0.17 ms with none ahead).
+constexpr int kAhead = 4;
+__global__ void __launch_bounds__(64) k_wline(const double2* __restrict__ canon, double2* wd, double2* poly, Geom g,
+                                              int64_t V, double b) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
   int p = blockIdx.y;
   if (s >= g.Vs2) return;
@@ -148,20 +124,34 @@ __global__ void k_wline(const double2* __restrict__ canon, double2* wd, double2*
   int64_t f3 = (int64_t)q.x + (int64_t)g.Lx * (q.y + (int64_t)g.Ly * q.z);
   int64_t Vs = (int64_t)g.Lx * g.Ly * g.Lz;
   double2* w = wd + (int64_t)p * 9 * V2;
+  const double2* line = canon + ((int64_t)3 * V + f3) * 9;
+  double2 buf[kAhead][9];
+#pragma unroll
+  for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+    for (int k = 0; k < 9; ++k) buf[a][k] = line[Vs * (g.Lt - 1 - a > 0 ? g.Lt - 1 - a : 0) * 9 + k];
   cx<double> acc[9], u[9], nw[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = cx<double>{(k % 4 == 0) ? 1.0 : 0.0, 0.0};
-  for (int t = g.Lt - 1; t >= 0; --t) {
-    int64_t i = p3_idx(g, t, s);
-    const double2* src = canon + ((int64_t)3 * V + f3 + Vs * t) * 9;
-    double ph = t == g.Lt - 1 ? b : 1.0;
+  for (int t0 = g.Lt - 1; t0 >= 0; t0 -= kAhead) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) u[k] = cx<double>{ph * src[k].x, ph * src[k].y};
-    mm3(u, acc, nw);
+    for (int a = 0; a < kAhead; ++a) {
+      const int t = t0 - a;
+      if (t < 0) break;
+      const int64_t i = p3_idx(g, t, s);
+      const double ph = t == g.Lt - 1 ? b : 1.0;
+      const int tn = t - kAhead > 0 ? t - kAhead : 0;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      acc[k] = nw[k];
-      w[(int64_t)k * V2 + i] = make_double2(nw[k].re, nw[k].im);
+      for (int k = 0; k < 9; ++k) {
+        u[k] = cx<double>{ph * buf[a][k].x, ph * buf[a][k].y};
+        buf[a][k] = line[Vs * tn * 9 + k];
+      }
+      mm3(u, acc, nw);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        acc[k] = nw[k];
+        w[(int64_t)k * V2 + i] = make_double2(nw[k].re, nw[k].im);
+      }
     }
   }
   double2* pl = poly + (int64_t)p * 9 * g.Vs2;
@@ -169,77 +159,95 @@ __global__ void k_wline(const double2* __restrict__ canon, double2* wd, double2*
   for (int k = 0; k < 9; ++k) pl[(int64_t)k * g.Vs2 + s] = make_double2(acc[k].re, acc[k].im);
 }
 
-// Axial-gauge links U^ax_mu(x) = W(x)^dag U'_mu(x) W(x+mu) with Omega = W^dag (Sec. II.C,
-// App. C): every time link becomes the identity except U^ax_t(Lt-1) = W(0) = P.
-// Writes the p3 layout (F64, F32).
-__global__ void k_axial_links(const double2* __restrict__ canon, const double2* __restrict__ wd,
-                              double2* u3d, float2* u3f, Geom g, int64_t V,
-                              double b, int* flags) {
-  int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int mu = blockIdx.y;
-  if (n >= V) return;
-  int x, y, z, t;
-  canon_coords(n, g, x, y, z, t);
-  int xs[4] = {x, y, z, t};
-  int ls[4] = {g.Lx, g.Ly, g.Lz, g.Lt};
-  xs[mu] = xs[mu] + 1 == ls[mu] ? 0 : xs[mu] + 1;
-  int pa, pb;
-  int64_t ia, ib;
-  site_pi(g, false, x, y, z, t, pa, ia);
-  site_pi(g, false, xs[0], xs[1], xs[2], xs[3], pb, ib);
-  int64_t V2 = V / 2;
+// The links' layouts, from one read of the canonical links: p4 planes (F64, F32; the 4D even-odd
+// operator) with the phase b folded into U_t(Lt-1), and p3 planes (F64, F32, F16) of the
+// axial-gauge links U^ax_mu(x) = W(x)^dag U'_mu(x) W(x+mu) with Omega = W^dag (Sec. II.C, App. C):
+// every time link becomes the identity except U^ax_t(Lt-1) = W(0) = P.  A workgroup handles the
+// 64 sites of a sub-block, wavefront mu one direction; bound by what it writes (1872 bytes per
+// site; 24^3x128: 2.9 ms in three kernels in canonical order, whose planes took 16 and 64 bytes
+// at a time).
+__global__ void __launch_bounds__(256) k_links(const double2* __restrict__ canon, const double2* __restrict__ wd,
+                                               double2* u3d, float2* u3f, __half2* u3h, double2* u4d, float2* u4f,
+                                               Geom g, int64_t V, double b, int* flags) {
+  const int lane = threadIdx.x & 63, mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const SubSite q = sub_site(g, lane);
+  if (!q.ok) return;
+  const C3 c = p3_coords(g, q.p, q.s);
+  const int t = q.t, pa = q.p;
+  const int xn = mu == 0 ? (c.x + 1 == g.Lx ? 0 : c.x + 1) : c.x;
+  const int yn = mu == 1 ? (c.y + 1 == g.Ly ? 0 : c.y + 1) : c.y;
+  const int zn = mu == 2 ? (c.z + 1 == g.Lz ? 0 : c.z + 1) : c.z;
+  const int tn = mu == 3 ? (t + 1 == g.Lt ? 0 : t + 1) : t;
+  const int64_t n = c.x + (int64_t)g.Lx * (c.y + (int64_t)g.Ly * (c.z + (int64_t)g.Lz * t));
+  const int64_t ia = p3_idx(g, t, q.s), V2 = g.V2;
+  int pb;
+  int64_t ib;
+  site_pi(g, false, xn, yn, zn, tn, pb, ib);
   cx<double> U[9], Wa[9], Wb[9], T1[9], T2[9];
-  double ph = (mu == 3 && t == g.Lt - 1) ? b : 1.0;
+  const double ph = (mu == 3 && t == g.Lt - 1) ? b : 1.0;
   const double2* src = canon + ((int64_t)mu * V + n) * 9;
   bool finite = true;
+#pragma unroll
   for (int k = 0; k < 9; ++k) {
-    finite = finite && isfinite(src[k].x) && isfinite(src[k].y);
-    U[k] = cx<double>{ph * src[k].x, ph * src[k].y};
-    double2 ea = wd[((int64_t)pa * 9 + k) * V2 + ia];
-    double2 eb = wd[((int64_t)pb * 9 + k) * V2 + ib];
+    const double2 e = src[k];
+    finite = finite && isfinite(e.x) && isfinite(e.y);
+    U[k] = cx<double>{ph * e.x, ph * e.y};
+    const double2 ea = wd[((int64_t)pa * 9 + k) * V2 + ia];
+    const double2 eb = wd[((int64_t)pb * 9 + k) * V2 + ib];
     Wa[k] = cx<double>{ea.x, -ea.y};  // conj, transposed below
     Wb[k] = cx<double>{eb.x, eb.y};
   }
+  {
+    const int p4 = pa ^ (t & 1);
+    const int64_t i4 = q.s + (int64_t)g.Vs2 * t, off = (int64_t)(mu * 2 + p4) * 9 * V2;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      u4d[off + (int64_t)k * V2 + i4] = make_double2(U[k].re, U[k].im);
+      u4f[off + comp_off<float2>(k, 9, V2, i4)] = make_float2(float(U[k].re), float(U[k].im));
+    }
+  }
   cx<double> Wad[9];
+#pragma unroll
   for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) Wad[3 * r + c] = Wa[3 * c + r];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) Wad[3 * r + k] = Wa[3 * k + r];
   mm3(Wad, U, T1);
   mm3(T1, Wb, T2);
-  {
-    // spatial links: deviation of the axial-frame link from SU(3); time links: deviation of
-    // the input link from unitarity (the axial frame is a gauge rotation only for unitary W)
-    const cx<double>* m = mu < 3 ? T2 : U;
-    double dev = 0;
-    for (int r = 0; r < 3; ++r)
-      for (int c = 0; c < 3; ++c) {
-        cx<double> e = cx<double>{r == c ? -1.0 : 0.0, 0.0};
-        for (int k = 0; k < 3; ++k) e += cmul(m[3 * r + k], conj(m[3 * c + k]));
-        dev = fmax(dev, sqrt(norm2(e)));
-      }
-    if (mu < 3) {
-      cx<double> c0 = cmul(m[4], m[8]) - cmul(m[5], m[7]);
-      cx<double> c1 = cmul(m[5], m[6]) - cmul(m[3], m[8]);
-      cx<double> c2 = cmul(m[3], m[7]) - cmul(m[4], m[6]);
-      cx<double> det = cmul(m[0], c0) + cmul(m[1], c1) + cmul(m[2], c2);
-      dev = fmax(dev, sqrt(norm2(det - cx<double>{1.0, 0.0})));
-      if (!(dev <= 1e-9)) flags[0] = 1;
-      if (!(dev <= 1e-13)) flags[3] = 1;
-    } else if (!(dev <= 1e-10)) {
-      flags[1] = 1;
-    }
-    if (!finite) flags[2] = 1;
-  }
-  double2* d3 = u3d + ((int64_t)(mu * 2 + pa) * 9) * V2 + ia;
-  float2* f3 = u3f + ((int64_t)(mu * 2 + pa) * 9) * V2;
+  const int64_t off = (int64_t)(mu * 2 + pa) * 9 * V2;
+#pragma unroll
   for (int k = 0; k < 9; ++k) {
-    d3[(int64_t)k * V2] = make_double2(T2[k].re, T2[k].im);
-    f3[comp_off<float2>(k, 9, V2, ia)] = make_float2(float(T2[k].re), float(T2[k].im));
+    const float2 f = make_float2(float(T2[k].re), float(T2[k].im));
+    u3d[off + (int64_t)k * V2 + ia] = make_double2(T2[k].re, T2[k].im);
+    u3f[off + comp_off<float2>(k, 9, V2, ia)] = f;
+    u3h[off + comp_off<__half2>(k, 9, V2, ia)] = __float22half2_rn(f);
   }
-}
-
-__global__ void k_to_half(const float2* __restrict__ src, __half2* __restrict__ dst, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = __float22half2_rn(src[i]);
+  // spatial links: deviation of the axial-frame link from SU(3); time links: deviation of
+  // the input link from unitarity (the axial frame is a gauge rotation only for unitary W)
+  cx<double> m[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) m[k] = mu < 3 ? T2[k] : U[k];
+  double dev = 0;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      cx<double> e = cx<double>{r == k ? -1.0 : 0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < 3; ++j) e += cmul(m[3 * r + j], conj(m[3 * k + j]));
+      dev = fmax(dev, sqrt(norm2(e)));
+    }
+  if (mu < 3) {
+    cx<double> c0 = cmul(m[4], m[8]) - cmul(m[5], m[7]);
+    cx<double> c1 = cmul(m[5], m[6]) - cmul(m[3], m[8]);
+    cx<double> c2 = cmul(m[3], m[7]) - cmul(m[4], m[6]);
+    cx<double> det = cmul(m[0], c0) + cmul(m[1], c1) + cmul(m[2], c2);
+    dev = fmax(dev, sqrt(norm2(det - cx<double>{1.0, 0.0})));
+    if (!(dev <= 1e-9)) flags[0] = 1;
+    if (!(dev <= 1e-13)) flags[3] = 1;
+  } else if (!(dev <= 1e-10)) {
+    flags[1] = 1;
+  }
+  if (!finite) flags[2] = 1;
 }
 
 TP_DEV bool inv3(const cx<double>* m, cx<double>* r) {
@@ -312,17 +320,6 @@ struct SigTab {
   double2 s[6][2][2][2];  // plane, chirality, row, col:  coef_p * V_chi^dag sigma_p V_chi / 2
 };
 
-TP_DEV void load_link(const double2* canon, const Geom& g, int64_t V, int mu, int x, int y, int z,
-                      int t, cx<double>* u) {
-  x = (x + g.Lx) % g.Lx;
-  y = (y + g.Ly) % g.Ly;
-  z = (z + g.Lz) % g.Lz;
-  t = (t + g.Lt) % g.Lt;
-  int64_t n = (int64_t)x + (int64_t)g.Lx * (y + (int64_t)g.Ly * (z + (int64_t)g.Lz * t));
-  const double2* src = canon + ((int64_t)mu * V + n) * 9;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) u[k] = cx<double>{src[k].x, src[k].y};
-}
 TP_DEV void chain4(const cx<double>* a, const cx<double>* b, const cx<double>* c,
                    const cx<double>* d, cx<double>* out) {
   cx<double> t1[9], t2[9];
@@ -552,20 +549,24 @@ TP_DEV void load_herm6_parts(const double2* base, int64_t st, int64_t i, double*
     lo[k] = cx<double>{v.x, v.y};
   }
 }
-TP_DEV void store_herm6_parts(const double* dg, const cx<double>* lo, double2* d, float2* f, int64_t st,
-                              int64_t i) {
+TP_DEV void store_herm6_parts(const double* dg, const cx<double>* lo, double2* d, float2* f, __half2* h,
+                              int64_t st, int64_t i) {
 #pragma unroll
   for (int slot = 0; slot < 18; ++slot) {
     const double2 v = slot < 3 ? make_double2(dg[2 * slot], dg[2 * slot + 1])
                                : make_double2(lo[slot - 3].re, lo[slot - 3].im);
     d[(int64_t)slot * st + i] = v;
-    if (f) f[comp_off<float2>(slot, 18, st, i)] = make_float2(float(v.x), float(v.y));
+    const float2 vf = make_float2(float(v.x), float(v.y));
+    f[comp_off<float2>(slot, 18, st, i)] = vf;
+    if (h) h[comp_off<__half2>(slot, 18, st, i)] = __float22half2_rn(vf);
   }
 }
 
-// From the stored A/2 blocks (layout p3 or p4), write (A+mu)/2 and (A+mu)^-1/2 blocks.
+// From the stored A/2 blocks (layout p3 or p4), write (A+mu)/2 and (A+mu)^-1/2 blocks (the FP16
+// copies of the p3 layout as well).
 __global__ void __launch_bounds__(64) k_clover_derived(const double2* __restrict__ a, double2* amu,
                                                        double2* ainv, float2* amu_f, float2* ainv_f,
+                                                       __half2* amu_h, __half2* ainv_h,
                                                        int64_t V2, double mu, int* bad) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int p = blockIdx.y;
@@ -585,7 +586,7 @@ __global__ void __launch_bounds__(64) k_clover_derived(const double2* __restrict
     }
 #pragma unroll
     for (int k = 0; k < 6; ++k) dg[k] += 0.5 * mu;  // (A + mu)/2
-    store_herm6_parts(dg, lo, amu + off, amu_f ? amu_f + off : nullptr, V2, i);
+    store_herm6_parts(dg, lo, amu + off, amu_f + off, amu_h ? amu_h + off : nullptr, V2, i);
     // (A+mu)^-1/2 = [(A+mu)/2]^-1 / 4
     if (!inv_herm6(dg, lo, idg, ilo)) {
       bad[0] = 1;
@@ -598,38 +599,61 @@ __global__ void __launch_bounds__(64) k_clover_derived(const double2* __restrict
     for (int k = 0; k < 6; ++k) idg[k] *= 0.25;
 #pragma unroll
     for (int k = 0; k < 15; ++k) ilo[k] = 0.25 * ilo[k];
-    store_herm6_parts(idg, ilo, ainv + off, ainv_f ? ainv_f + off : nullptr, V2, i);
+    store_herm6_parts(idg, ilo, ainv + off, ainv_f + off, ainv_h ? ainv_h + off : nullptr, V2, i);
   }
 }
 
-// Plaquette averages (1/3 Re tr) over spatial and temporal planes: per-block partials.
-__global__ void k_plaquette(const double2* __restrict__ canon, Geom g, int64_t V, double* part) {
-  __shared__ double sh[2][kBlock];
-  int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Plaquette averages (1/3 Re tr) over spatial and temporal planes: a workgroup handles the 64
+// sites of a sub-block, each of its three wavefronts two planes, and writes one partial pair;
+// Re tr(U_mu(x) U_nu(x+mu) [U_nu(x) U_mu(x+nu)]^dag) needs two products and a sum.  Bound by the
+// links' reads (24^3x128: 2.1 ms from canonical links, one cache line per lane and load).
+__global__ void __launch_bounds__(192) k_plaquette(const double2* __restrict__ u4, Geom g, double* part) {
+  __shared__ double sh[3][2];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const SubSite q = sub_site(g, lane);
+  const C3 c = p3_coords(g, q.p, q.s);
   double ps = 0, pt = 0;
-  if (n < V) {
-    int x, y, z, t;
-    canon_coords(n, g, x, y, z, t);
-    // planes 01 02 12 03 13 23; offsets formed arithmetically, not from a table indexed by
-    // the plane (which would live in scratch memory)
+  // planes 01 02 | 12 03 | 13 23; offsets formed arithmetically, not from a table indexed by
+  // the plane (which would live in scratch memory)
 #pragma unroll 1
-    for (int pl = 0; pl < 6; ++pl) {
-      const int mu = pl == 2 || pl == 4 ? 1 : (pl == 5 ? 2 : 0);
-      const int nu = pl < 3 ? (pl == 0 ? 1 : 2) : 3;
-      cx<double> a[9], b[9], c[9], d[9], cd[9], dd[9], leaf[9];
-      load_link(canon, g, V, mu, x, y, z, t, a);
-      load_link(canon, g, V, nu, x + (mu == 0), y + (mu == 1), z + (mu == 2), t + (mu == 3), b);
-      load_link(canon, g, V, mu, x + (nu == 0), y + (nu == 1), z + (nu == 2), t + (nu == 3), c);
-      load_link(canon, g, V, nu, x, y, z, t, d);
-      dag3(c, cd);
-      dag3(d, dd);
-      chain4(a, b, cd, dd, leaf);
-      double re = (leaf[0].re + leaf[4].re + leaf[8].re) / 3.0;
-      if (pl < 3) ps += re; else pt += re;
-    }
+  for (int pl = 2 * wave; pl < 2 * wave + 2; ++pl) {
+    const int mu = pl == 2 || pl == 4 ? 1 : (pl == 5 ? 2 : 0);
+    const int nu = pl < 3 ? (pl == 0 ? 1 : 2) : 3;
+    cx<double> a[9], b[9], m[9], n[9];
+    load_soa<false>(u4, g, mu, c.x, c.y, c.z, q.t, a);
+    load_soa<false>(u4, g, nu, c.x + (mu == 0), c.y + (mu == 1), c.z + (mu == 2), q.t, b);
+    mm3(a, b, m);
+    load_soa<false>(u4, g, nu, c.x, c.y, c.z, q.t, a);
+    load_soa<false>(u4, g, mu, c.x, c.y + (nu == 1), c.z + (nu == 2), q.t + (nu == 3), b);
+    mm3(a, b, n);
+    double re = 0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) re += m[k].re * n[k].re + m[k].im * n[k].im;
+    re /= 3.0;
+    if (!q.ok) re = 0;
+    if (pl < 3) ps += re; else pt += re;
   }
-  sh[0][threadIdx.x] = ps;
-  sh[1][threadIdx.x] = pt;
+  for (int off = 32; off > 0; off >>= 1) {
+    ps += __shfl_xor(ps, off);
+    pt += __shfl_xor(pt, off);
+  }
+  if (lane == 0) {
+    sh[wave][0] = ps;
+    sh[wave][1] = pt;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) part[2 * (int64_t)blockIdx.x + threadIdx.x] = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x];
+}
+// Sums the n partial pairs into the pair behind them.
+__global__ void __launch_bounds__(kBlock) k_plaquette_sum(double* part, int64_t n) {
+  __shared__ double sh[2][kBlock];
+  double v[2] = {0, 0};
+  for (int64_t k = threadIdx.x; k < n; k += kBlock) {
+    v[0] += part[2 * k];
+    v[1] += part[2 * k + 1];
+  }
+  sh[0][threadIdx.x] = v[0];
+  sh[1][threadIdx.x] = v[1];
   __syncthreads();
   for (int w = kBlock / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) {
@@ -638,10 +662,7 @@ __global__ void k_plaquette(const double2* __restrict__ canon, Geom g, int64_t V
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = sh[0][0];
-    part[2 * blockIdx.x + 1] = sh[1][0];
-  }
+  if (threadIdx.x < 2) part[2 * n + threadIdx.x] = sh[threadIdx.x][0];
 }
 
 inline unsigned nblk(int64_t n, int64_t b = kBlock) { return (unsigned)((n + b - 1) / b); }
@@ -682,31 +703,17 @@ void launch_unpack(tp_ctx ctx, const Field& src, double2* canon, bool l4, bool g
   }
 }
 
-void launch_pack_links(tp_ctx ctx, tp_gauge g) {
+void launch_wline(tp_ctx ctx, tp_gauge g, const double2* links) {
   const Lattice& L = ctx->lat;
-  hipLaunchKernelGGL(k_pack_links4, dim3(nblk(L.V), 4), dim3(kBlock), 0, ctx->stream, g->canon,
-                     g->u4_d, g->u4_f, L.g, L.V, double(ctx->bc));
+  hipLaunchKernelGGL(k_wline, dim3((L.Vs2 + 63) / 64, 2), dim3(64), 0, ctx->stream, links, g->w_d, g->poly, L.g,
+                     L.V, double(ctx->bc));
   LAUNCH_CHECK();
 }
 
-void launch_wline(tp_ctx ctx, tp_gauge g) {
+void launch_links(tp_ctx ctx, tp_gauge g, const double2* links, int* flags) {
   const Lattice& L = ctx->lat;
-  hipLaunchKernelGGL(k_wline, dim3((L.Vs2 + 63) / 64, 2), dim3(64), 0, ctx->stream, g->canon,
-                     g->w_d, g->poly, L.g, L.V, double(ctx->bc));
-  LAUNCH_CHECK();
-}
-
-void launch_to_half(tp_ctx ctx, const float2* src, __half2* dst, int64_t n) {
-  int64_t nb = (n + 255) / 256;
-  if (nb > 65536) nb = 65536;
-  hipLaunchKernelGGL(k_to_half, dim3((unsigned)nb), dim3(256), 0, ctx->stream, src, dst, n);
-  LAUNCH_CHECK();
-}
-
-void launch_axial_links(tp_ctx ctx, tp_gauge g, int* flags) {
-  const Lattice& L = ctx->lat;
-  hipLaunchKernelGGL(k_axial_links, dim3(nblk(L.V, 64), 4), dim3(64), 0, ctx->stream, g->canon,
-                     g->w_d, g->u3_d, g->u3_f, L.g, L.V, double(ctx->bc), flags);
+  hipLaunchKernelGGL(k_links, dim3(sub_blocks(L)), dim3(256), 0, ctx->stream, links, g->w_d, g->u3_d, g->u3_f,
+                     g->u3_h, g->u4_d, g->u4_f, L.g, L.V, double(ctx->bc), flags);
   LAUNCH_CHECK();
 }
 
@@ -742,16 +749,20 @@ void launch_clover_derived(tp_ctx ctx, tp_op op, int* bad) {
   const double2* a4 = op->c ? op->c->a4_d : nullptr;
   const double2* a3 = op->c ? op->c->a3_d : nullptr;
   hipLaunchKernelGGL(k_clover_derived, dim3(nblk(L.V2, 64), 2), dim3(64), 0, ctx->stream, a4,
-                     op->a4_mu, op->a4_inv, op->a4_mu_f, op->a4_inv_f, L.V2, op->mu, bad);
+                     op->a4_mu, op->a4_inv, op->a4_mu_f, op->a4_inv_f, (__half2*)nullptr,
+                     (__half2*)nullptr, L.V2, op->mu, bad);
   LAUNCH_CHECK();
   hipLaunchKernelGGL(k_clover_derived, dim3(nblk(L.V2, 64), 2), dim3(64), 0, ctx->stream, a3,
-                     op->a3_mu, op->a3_inv, op->a3_mu_f, op->a3_inv_f, L.V2, op->mu, bad);
+                     op->a3_mu, op->a3_inv, op->a3_mu_f, op->a3_inv_f, op->a3_mu_h, op->a3_inv_h,
+                     L.V2, op->mu, bad);
   LAUNCH_CHECK();
 }
 
+int64_t plaquette_partials(tp_ctx ctx) { return sub_blocks(ctx->lat); }
 void launch_plaquette(tp_ctx ctx, tp_gauge g, double* part) {
   const Lattice& L = ctx->lat;
-  hipLaunchKernelGGL(k_plaquette, dim3(nblk(L.V)), dim3(kBlock), 0, ctx->stream, g->canon, L.g,
-                     L.V, part);
+  hipLaunchKernelGGL(k_plaquette, dim3(sub_blocks(L)), dim3(192), 0, ctx->stream, g->u4_d, L.g, part);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_plaquette_sum, dim3(1), dim3(kBlock), 0, ctx->stream, part, plaquette_partials(ctx));
   LAUNCH_CHECK();
 }

@@ -137,7 +137,6 @@ struct tp_ctx_s {
 
 struct tp_gauge_s {
   tp_ctx ctx = nullptr;
-  double2* canon = nullptr;  // device copy of the canonical links [4][V][9]
   // p3 layout [4 dir][2 par][9][V2] in the axial gauge W(x)^dag U(x) W(x+mu): interior
   // time links are the identity, U_t(Lt-1) = P (Polyakov loop with the phase b)
   double2* u3_d = nullptr;
@@ -241,18 +240,19 @@ void launch_pack(tp_ctx ctx, const double2* canon, Field& dst, bool layout4, boo
                  const double2* w);
 void launch_unpack(tp_ctx ctx, const Field& src, double2* canon, bool layout4, bool gamma5,
                    const double2* w);
-void launch_pack_links(tp_ctx ctx, tp_gauge g);   // p4 layout (original frame)
-void launch_wline(tp_ctx ctx, tp_gauge g);        // W(t), P from the canonical links
-// p3 layout, axial frame.  flags: three device ints zeroed by the caller; [0] is set when an
-// axial-frame spatial link deviates from SU(3) by more than 1e-9, [1] when a time link
-// deviates from unitarity by more than 1e-10, [2] when an input entry is NaN or Inf
-void launch_axial_links(tp_ctx ctx, tp_gauge g, int* flags);
-// dst = src rounded to FP16 (n complex values)
-void launch_to_half(tp_ctx ctx, const float2* src, __half2* dst, int64_t n);
+// links: device pointer to the canonical links [4][V][9]
+void launch_wline(tp_ctx ctx, tp_gauge g, const double2* links);  // W(t), P
+// the p4 planes (original frame) and the p3 planes (axial frame).  flags: four device ints zeroed
+// by the caller; [0] is set when an axial-frame spatial link deviates from SU(3) by more than
+// 1e-9 ([3]: 1e-13), [1] when a time link deviates from unitarity by more than 1e-10, [2] when
+// an input entry is NaN or Inf
+void launch_links(tp_ctx ctx, tp_gauge g, const double2* links, int* flags);
 void launch_closure(tp_ctx ctx, tp_op op, double* cond_out /*device [2*Vs2]*/);
 void launch_clover_build(tp_ctx ctx, tp_clover c, const double sig[6][2][2][2][2]);
 void launch_clover_derived(tp_ctx ctx, tp_op op, int* bad /*device counter*/);
-void launch_plaquette(tp_ctx ctx, tp_gauge g, double* out2 /*device partial sums*/);
+int64_t plaquette_partials(tp_ctx ctx);
+// part: plaquette_partials() + 1 device pairs; the last receives the sums over space and time planes
+void launch_plaquette(tp_ctx ctx, tp_gauge g, double* part);
 
 // ---------------------------------------------------------------- launchers (operators)
 // p3 site kernel: dst = c_mu*src + c_A*(A src) + c_t*(D_t src) + c_s*(D_s src) + c_in*in2,

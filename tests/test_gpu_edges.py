@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import synth
-from oracle import force as oforce
+from oracle import force as oforce, wilson
 from oracle.schemes import Operator as OOp
 
 pytestmark = pytest.mark.gpu
@@ -27,6 +27,10 @@ def _make(dims, xi=3.0, m0=0.05, cs=1.6, ct=1.0, bc=-1, seed=1100):
 def _rel(a, b):
     a = a.cpu().numpy()
     return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def _dag(m):
+    return np.conj(np.swapaxes(m, -1, -2))
 
 
 # sub-blocks of the set-up kernels are 16 spatial indices (of one parity) x 4 slices
@@ -58,4 +62,29 @@ def test_link_gradient(dims, bc):
     for (raw, proj), only in ((oforce.link_gradient(o, x, lam), True), (oforce.full_link_gradient(o, x, lam), False)):
         assert _rel(g.force(tx, tl, projected=False, hopping_only=only), raw) < TOL64
         assert _rel(g.force(tx, tl, projected=True, hopping_only=only), proj) < TOL64
+    g.close()
+
+
+@pytest.mark.parametrize("dims", SUB_DIMS)
+@pytest.mark.parametrize("host", [True, False])
+def test_links_and_plaquette(dims, host):
+    """Every layout of the links (M in the axial frame and, through the 4D scheme, the original
+    one, in F64 and F32) from host and device links, and the plaquette."""
+    from paper_0910_0992_amd import Operator
+    U = synth.make_links(dims, 0.35, 0.2, 1101)
+    o = OOp(U, 0.05, 3.0, -1.0, 0.5, 1.0)
+    tu = torch.from_numpy(U)
+    g = Operator(tu if host else tu.cuda(), 0.05, 3.0, 0.5, 1.0, -1)
+    eta = synth.make_source(dims, 2103)
+    t = torch.from_numpy(eta).cuda()
+    for prec, tol in (("F64", TOL64), ("F32", 6e-6)):
+        assert _rel(g.apply_M(t, prec), o.M(eta)) < tol
+        if dims[3] % 2 == 0:
+            assert _rel(g.apply_prec(t, "SCHUR4D", prec), o.prec("SCHUR4D", eta)) < tol
+    tr = lambda m: np.trace(m, axis1=-2, axis2=-1).real.mean() / 3
+    pl = lambda a, b: tr(wilson._chain([U[a], wilson.link_shift(U[b], a, 1), _dag(wilson.link_shift(U[a], b, 1)),
+                                        _dag(U[b])]))
+    ps, pt = g.plaquette()
+    assert abs(ps - (pl(0, 1) + pl(0, 2) + pl(1, 2)) / 3) < 1e-13
+    assert abs(pt - (pl(0, 3) + pl(1, 3) + pl(2, 3)) / 3) < 1e-13
     g.close()
