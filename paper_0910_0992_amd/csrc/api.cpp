@@ -182,10 +182,7 @@ void dev_free(tp_ctx ctx, void* p) {
 }
 
 size_t field_bytes(const Lattice& lat, int prec, int nr) {
-  const size_t eb = prec == TP_F64 ? 16 : (prec == TP_F32 ? 8 : 4);
-  size_t db = (size_t(nr) * 2 * 12 * lat.V2 * eb + 255) & ~size_t(255);
-  if (prec == TP_F16N) db += (size_t(nr) * 2 * 2 * lat.V2 * sizeof(float) + 255) & ~size_t(255);
-  return db;
+  return (size_t(nr) * 4 * Field::half_bytes(prec) * lat.V2 + 255) & ~size_t(255);
 }
 
 Field field_alloc(tp_ctx ctx, int prec, int nr) {
@@ -194,24 +191,15 @@ Field field_alloc(tp_ctx ctx, int prec, int nr) {
   f.prec = prec;
   f.V2 = lat.V2;
   f.nr = nr;
-  const size_t db = size_t(nr) * 2 * 12 * lat.V2 * f.elem_bytes();
+  const size_t db = size_t(nr) * 4 * Field::half_bytes(prec) * lat.V2;
   f.data = dev_alloc(ctx, db);
   f.owned = true;
   HIP_CHECK(hipMemsetAsync(f.data, 0, db, ctx->stream));
-  if (prec == TP_F16N) {
-    const size_t nb = size_t(nr) * 2 * 2 * lat.V2 * sizeof(float);
-    f.nrm = static_cast<float*>(dev_alloc(ctx, nb));
-    HIP_CHECK(hipMemsetAsync(f.nrm, 0, nb, ctx->stream));
-  }
   return f;
 }
 void field_free(tp_ctx ctx, Field& f) {
-  if (f.owned) {
-    dev_free(ctx, f.data);
-    dev_free(ctx, f.nrm);
-  }
+  if (f.owned) dev_free(ctx, f.data);
   f.data = nullptr;
-  f.nrm = nullptr;
 }
 
 ProfScope::ProfScope(tp_ctx c, int k, double b)
@@ -350,11 +338,10 @@ void check_tpfield(tp_op op, const tp_field* f, const char* what) {
 
 size_t tpfield_bytes(const Lattice& L, int layout, int prec, int subset) {
   if (layout == TP_LAYOUT_CANONICAL) return size_t(L.V) * 12 * sizeof(double2);
-  const size_t eb = prec == TP_F64 ? 16 : (prec == TP_F32 ? 8 : 4);
   const size_t npar = subset == TP_SUBSET_FULL ? 2 : 1;
-  size_t b = al256(npar * 12 * L.V2 * eb);
-  if (prec == TP_F16N) b += al256(npar * 2 * L.V2 * sizeof(float));
-  return b;
+  // F16N: the room of its values and of its scales, each rounded up (the planes hold both)
+  if (prec == TP_F16N) return al256(npar * 48 * L.V2) + al256(npar * 8 * L.V2);
+  return al256(npar * 2 * Field::half_bytes(prec) * L.V2);
 }
 
 // Right-hand side r of an internal field as a Field.  For a one-parity field, parity p of the
@@ -369,12 +356,8 @@ Field tpfield_view(const Lattice& L, const tp_field& f, int r) {
   v.owned = false;
   const size_t per = tpfield_bytes(L, f.layout, f.prec, f.subset);
   const uintptr_t base = reinterpret_cast<uintptr_t>(f.data) + size_t(r) * per;
-  const size_t npar = f.subset == TP_SUBSET_FULL ? 2 : 1;
-  const size_t dbytes = al256(npar * 12 * L.V2 * v.elem_bytes());
-  const int p = f.subset == TP_SUBSET_ODD ? 1 : 0;
-  const uintptr_t back = f.subset == TP_SUBSET_FULL ? 0 : uintptr_t(p);
-  v.data = reinterpret_cast<void*>(base - back * 12 * L.V2 * v.elem_bytes());
-  v.nrm = f.prec == TP_F16N ? reinterpret_cast<float*>(base + dbytes - back * 2 * L.V2 * sizeof(float)) : nullptr;
+  const uintptr_t back = f.subset == TP_SUBSET_ODD ? 1 : 0;
+  v.data = reinterpret_cast<void*>(base - back * 2 * Field::half_bytes(f.prec) * L.V2);
   return v;
 }
 

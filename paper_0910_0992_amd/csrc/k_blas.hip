@@ -44,53 +44,8 @@ TP_DEV void block_reduce(double (&acc)[8], int nred, double* partial, uint32_t b
 
 template <typename R> TP_DEV cx<R> cc(const double* z) { return cx<R>{R(z[0]), R(z[1])}; }
 
-// Streaming access for the reductions that write no field (norms and inner products): each field
-// is read once, in vectors larger than the caches, so the loads carry the non-temporal hint.
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename T> TP_DEV T nt_load(const T* p) {
-  if constexpr (sizeof(T) == 16) {
-    return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
-  } else if constexpr (sizeof(T) == 8) {
-    return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)));
-  } else {
-    static_assert(sizeof(T) == 4, "4, 8 or 16 bytes");
-    return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p)));
-  }
-}
-// load_half of tp_device.h with non-temporal accesses (same values).
-template <typename S, typename R = typename Prec<S>::R>
-TP_DEV void nt_load_half(const SpinorF<S>& f, int h, uint32_t i, cx<R>* v) {
-  const S* b = f.p[h];
-  if constexpr (Prec<S>::half) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const Half2x2 e = nt_load(reinterpret_cast<const Half2x2*>(at(b + (int64_t)(2 * q) * f.stride, 2 * i)));
-      const float2 fa = __half22float2(e.a), fb = __half22float2(e.b);
-      v[2 * q] = {fa.x, fa.y};
-      v[2 * q + 1] = {fb.x, fb.y};
-    }
-    const R sc = nt_load(at(f.nrm[h], i));
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = sc * v[c];
-  } else if constexpr (paired<S>()) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float4 e = nt_load(reinterpret_cast<const float4*>(at(b + (int64_t)(2 * q) * f.stride, 2 * i)));
-      v[2 * q] = {e.x, e.y};
-      v[2 * q + 1] = {e.z, e.w};
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      const S e = nt_load(at(b + (int64_t)c * f.stride, i));
-      v[c] = {R(e.x), R(e.y)};
-    }
-  }
-}
-
-
-
+// The reductions that write no field (norms and inner products) read each field once, in vectors
+// larger than the caches: their loads carry the non-temporal hint (nt_load_half).
 
 // acc[0..1] += <x, y> = sum conj(x) y over one half spinor, in FP64.
 template <typename R>

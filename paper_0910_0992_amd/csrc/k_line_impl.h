@@ -300,44 +300,8 @@ TP_DEV void scan_core(cx<R> (&v)[CH][NV], cx<R>* lds, ScanCtx<R>& sc) {
 }
 
 // The line kernels read every input once per launch (the middle kernel parks what it needs
-// twice in LDS), in fields larger than the caches: their loads carry the non-temporal hint.
-typedef unsigned int lu32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int lu32x4 __attribute__((ext_vector_type(4)));
-template <typename T> TP_DEV T nt_ld(const T* p) {
-  if constexpr (sizeof(T) == 16) return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const lu32x4*>(p)));
-  else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const lu32x2*>(p)));
-  else return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p)));
-}
-// load_half (64-bit index form) with non-temporal loads: the same values.
-template <typename S, typename R = typename Prec<S>::R>
-TP_DEV void nt_load_half(const SpinorF<S>& f, int h, int64_t i, cx<R>* v) {
-  const S* b = f.p[h];
-  if constexpr (Prec<S>::half) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const Half2x2 e = nt_ld(reinterpret_cast<const Half2x2*>(b + (int64_t)(2 * q) * f.stride + 2 * i));
-      const float2 fa = __half22float2(e.a), fb = __half22float2(e.b);
-      v[2 * q] = {fa.x, fa.y};
-      v[2 * q + 1] = {fb.x, fb.y};
-    }
-    const R sc = nt_ld(f.nrm[h] + i);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = sc * v[c];
-  } else if constexpr (paired<S>()) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float4 e = nt_ld(reinterpret_cast<const float4*>(b + (int64_t)(2 * q) * f.stride + 2 * i));
-      v[2 * q] = {e.x, e.y};
-      v[2 * q + 1] = {e.z, e.w};
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      const S e = nt_ld(b + (int64_t)c * f.stride + i);
-      v[c] = {R(e.x), R(e.y)};
-    }
-  }
-}
+// twice in LDS), in fields larger than the caches: their loads carry the non-temporal hint
+// (nt_load_half).
 
 template <int N> struct Arr { static constexpr int n = N > 0 ? N : 1; };
 
@@ -572,9 +536,11 @@ struct RawHalf {
 
   TP_DEV void load(const SpinorF<S>& f, int h, int64_t i) {
     if constexpr (half) {
+      HalfRaw r;
+      load_half_raw<true>(r, f, h, i);
 #pragma unroll
-      for (int q = 0; q < 3; ++q) e[q] = nt_ld(reinterpret_cast<const Half2x2*>(f.p[h] + (int64_t)(2 * q) * f.stride + 2 * i));
-      s = nt_ld(f.nrm[h] + i);
+      for (int q = 0; q < 3; ++q) e[q] = r.e[q];
+      s = r.s;
     } else {
       nt_load_half<S, R>(f, h, i, e);
     }
@@ -591,12 +557,7 @@ struct RawHalf {
   }
   TP_DEV void unpack(cx<R>* v) const {
     if constexpr (half) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const float2 fa = __half22float2(e[q].a), fb = __half22float2(e[q].b);
-        v[2 * q] = {s * fa.x, s * fa.y};
-        v[2 * q + 1] = {s * fb.x, s * fb.y};
-      }
+      HalfRaw{{e[0], e[1], e[2]}, s}.unpack(v);
     } else {
 #pragma unroll
       for (int c = 0; c < 6; ++c) v[c] = e[c];
@@ -867,7 +828,6 @@ void line_t(tp_op op, int par, const LineIO& io, Field& dst) {
   SpinorF<S> up = pv<S>(io.in_up, par), lo = pv<S>(io.in_lo, par);
   a.in = up;
   a.in.p[1] = lo.p[1];
-  a.in.nrm[1] = lo.nrm[1];
   a.out = pv<S>(&dst, par);
   a.base = pv<S>(io.base, par);
   a.nr = dst.nr;

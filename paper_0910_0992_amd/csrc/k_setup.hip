@@ -686,7 +686,7 @@ void unpack_t(tp_ctx ctx, const Field& src, double2* canon, bool l4, bool g5, co
 }  // namespace
 
 void launch_pack(tp_ctx ctx, const double2* canon, Field& dst, bool l4, bool g5, const double2* w) {
-  ProfScope ps(ctx, KID_PACK, double(ctx->lat.V) * (192 + 12 * dst.elem_bytes() + (w ? 144 : 0)));
+  ProfScope ps(ctx, KID_PACK, double(ctx->lat.V) * (192 + 2 * Field::half_bytes(dst.prec) + (w ? 144 : 0)));
   switch (dst.prec) {
     case TP_F64: pack_t<double2>(ctx, canon, dst, l4, g5, w); break;
     case TP_F32: pack_t<float2>(ctx, canon, dst, l4, g5, w); break;
@@ -695,7 +695,7 @@ void launch_pack(tp_ctx ctx, const double2* canon, Field& dst, bool l4, bool g5,
 }
 
 void launch_unpack(tp_ctx ctx, const Field& src, double2* canon, bool l4, bool g5, const double2* w) {
-  ProfScope ps(ctx, KID_PACK, double(ctx->lat.V) * (192 + 12 * src.elem_bytes() + (w ? 144 : 0)));
+  ProfScope ps(ctx, KID_PACK, double(ctx->lat.V) * (192 + 2 * Field::half_bytes(src.prec) + (w ? 144 : 0)));
   switch (src.prec) {
     case TP_F64: unpack_t<double2>(ctx, src, canon, l4, g5, w); break;
     case TP_F32: unpack_t<float2>(ctx, src, canon, l4, g5, w); break;

@@ -182,7 +182,6 @@ SpinorF<S> view(const Field* f, int p) {
   if (!f) {
     SpinorF<S> z;
     z.p[0] = z.p[1] = nullptr;
-    z.nrm[0] = z.nrm[1] = nullptr;
     z.stride = 0;
     return z;
   }
@@ -261,7 +260,6 @@ template <typename S>
 SpinorF<S> halves(const Field* up, const Field* lo, int p) {
   SpinorF<S> a = view<S>(up, p), b = view<S>(lo, p);
   a.p[1] = b.p[1];
-  a.nrm[1] = b.nrm[1];
   if (!up) a.stride = b.stride;
   return a;
 }
@@ -394,7 +392,7 @@ void launch_schur4d(tp_op op, int prec, int mode, int p, const Field* src, Field
                     double c_h, double c_in, int ck) {
   tp_ctx ctx = op->g->ctx;
   const Lattice& L = ctx->lat;
-  double S = double(dst.elem_bytes()) * 12;
+  double S = 2.0 * Field::half_bytes(prec);
   double Lb = prec == TP_F64 ? 144 : 72;
   double C = prec == TP_F64 ? 576 : 288;
   double bytes = double(L.V2) * (S + (mode != 4 ? S + 8 * Lb : 0) + (in2 ? S : 0) + (ck ? C : 0));

@@ -60,10 +60,6 @@ Field& arena_get(tp_op op, int prec, int slot, int nr) {
   f.V2 = lat.V2;
   f.nr = nr;
   f.data = op->arena + op->arena_top;
-  if (prec == TP_F16N) {
-    const size_t db = size_t(nr) * 2 * 12 * lat.V2 * f.elem_bytes();
-    f.nrm = reinterpret_cast<float*>(op->arena + op->arena_top + ((db + 255) & ~size_t(255)));
-  }
   f.owned = false;
   op->arena_top += need;
   auto& a = op->arena_slots[op->arena_n++];

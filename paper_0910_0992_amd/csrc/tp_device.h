@@ -88,13 +88,23 @@ template <typename R> TP_DEV void st(float2* p, cx<R> v) { *p = make_float2(floa
 template <typename R> TP_DEV void st(__half2* p, cx<R> v) { *p = __floats2half2_rn(float(v.re), float(v.im)); }
 
 // ---- field storage --------------------------------------------------------------------------
-// A field of n complex components per site is stored as planes of `stride` sites.  FP32 and
-// FP16 fields pair the planes (2k, 2k+1): the two values of one site are adjacent, so a
-// single 16-byte (FP32) or 8-byte (FP16) load fetches both, halving the load instructions of
-// the bandwidth-bound kernels.  A last odd plane (links: 9 components) stays single.  FP64
-// fields keep one plane per component (a pair would exceed one 16-byte load).
-template <typename T> TP_HD constexpr bool paired() { return sizeof(T) <= 8; }
+// A field of n complex components per site is stored as planes of `stride` sites.  FP32 fields
+// pair the planes (2k, 2k+1): the two values of one site are adjacent, so a single 16-byte load
+// fetches both, halving the load instructions of the bandwidth-bound kernels.  A last odd plane
+// (links: 9 components) stays single.  FP64 fields keep one plane per component (a pair would
+// exceed one 16-byte load).
+// FP16 fields group four components (16 bytes): the vector memory unit takes one cycle per four
+// lanes' addresses whatever their width, so the hops, which keep it busy 90% of their time, are
+// the faster the fewer loads they need.  Links (9 components) are a group of four, two pairs and
+// a single, so that two rows are one 16- and one 8-byte load; clover blocks (18) four groups of
+// four and a pair.  Spinors are described below.
+template <typename T> TP_HD constexpr bool paired() { return sizeof(T) == 8; }
 template <typename T> TP_HD int64_t comp_off(int c, int n, int64_t stride, int64_t i) {
+  if (sizeof(T) == 4) {
+    const int first = n == 9 ? (c < 4 ? 0 : (c < 8 ? (c & ~1) : 8)) : (c < 16 ? (c & ~3) : 16);
+    const int size = n == 9 ? (c < 4 ? 4 : (c < 8 ? 2 : 1)) : (c < 16 ? 4 : 2);
+    return (int64_t)first * stride + (int64_t)size * i + (c - first);
+  }
   if (paired<T>() && c < (n & ~1)) return (int64_t)(c & ~1) * stride + 2 * i + (c & 1);
   return (int64_t)c * stride + i;
 }
@@ -106,42 +116,99 @@ template <> TP_DEV void ld2<float, float2>(const float2* p, cx<float>& a, cx<flo
   b = {v.z, v.w};
 }
 struct alignas(8) Half2x2 { __half2 a, b; };
-template <> TP_DEV void ld2<float, __half2>(const __half2* p, cx<float>& a, cx<float>& b) {
-  const Half2x2 v = *reinterpret_cast<const Half2x2*>(p);
-  const float2 fa = __half22float2(v.a), fb = __half22float2(v.b);
-  a = {fa.x, fa.y};
-  b = {fb.x, fb.y};
+
+// Loads of 8, 12 and 16 bytes, plain or with the non-temporal hint (fields read once, in passes
+// larger than the caches).
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT, typename T> TP_DEV T ld_vec(const T* p) {
+  if constexpr (!NT) {
+    return *p;
+  } else if constexpr (sizeof(T) == 16) {
+    return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+  } else if constexpr (sizeof(T) == 8) {
+    return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)));
+  } else {
+    static_assert(sizeof(T) == 4, "4, 8 or 16 bytes");
+    return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p)));
+  }
+}
+struct alignas(16) Half2x4 { Half2x2 a, b; };
+
+// An FP16 half spinor in storage form: six complex values and their FP32 scale, 28 bytes in two
+// planes: components 0-3 (16 bytes a site) and components 4-5 with the scale (12 bytes a site),
+// one load each.
+struct HalfRaw {
+  Half2x2 e[3];
+  float s;
+  TP_DEV void unpack(cx<float>* v) const {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const float2 fa = __half22float2(e[q].a), fb = __half22float2(e[q].b);
+      v[2 * q] = {s * fa.x, s * fa.y};
+      v[2 * q + 1] = {s * fb.x, s * fb.y};
+    }
+  }
+};
+// p: the four components of a site, t: its 12-byte entry
+template <bool NT> TP_DEV void ld_half_raw(HalfRaw& r, const __half2* p, const __half2* t) {
+  const Half2x4 v = ld_vec<NT>(reinterpret_cast<const Half2x4*>(p));
+  r.e[0] = v.a;
+  r.e[1] = v.b;
+  const unsigned* w = reinterpret_cast<const unsigned*>(t);
+  const unsigned w0 = ld_vec<NT>(w), w1 = ld_vec<NT>(w + 1), w2 = ld_vec<NT>(w + 2);
+  r.e[2] = Half2x2{__builtin_bit_cast(__half2, w0), __builtin_bit_cast(__half2, w1)};
+  r.s = __builtin_bit_cast(float, w2);
+}
+TP_DEV void st_half_raw(const HalfRaw& r, __half2* p, __half2* t) {
+  Half2x4 v;
+  v.a = r.e[0];
+  v.b = r.e[1];
+  *reinterpret_cast<Half2x4*>(p) = v;
+  unsigned* w = reinterpret_cast<unsigned*>(t);
+  w[0] = __builtin_bit_cast(unsigned, r.e[2].a);
+  w[1] = __builtin_bit_cast(unsigned, r.e[2].b);
+  w[2] = __builtin_bit_cast(unsigned, r.s);
+}
+// Storage form of six values: the scale is the largest component.  Below the smallest normal
+// FP32 value 1/m would overflow (a point source decaying as mu^-t along a long line gets there):
+// such a half spinor is stored as zero.  A NaN fails the comparison and propagates.
+TP_DEV HalfRaw half_raw_of(const cx<float>* v) {
+  float m = 0.f;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) m = fmaxf(m, fmaxf(fabsf(v[c].re), fabsf(v[c].im)));
+  if (m < 1.17549435e-38f) m = 0.f;
+  const float inv = m > 0.f ? 1.f / m : 0.f;
+  HalfRaw r;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const cx<float> a = inv * v[2 * q], b = inv * v[2 * q + 1];
+    r.e[q].a = __floats2half2_rn(a.re, a.im);
+    r.e[q].b = __floats2half2_rn(b.re, b.im);
+  }
+  r.s = m;
+  return r;
 }
 template <typename R> TP_DEV void st2(float2* p, cx<R> a, cx<R> b) {
   *reinterpret_cast<float4*>(p) = make_float4(float(a.re), float(a.im), float(b.re), float(b.im));
 }
-template <typename R> TP_DEV void st2(__half2* p, cx<R> a, cx<R> b) {
-  Half2x2 v;
-  v.a = __floats2half2_rn(float(a.re), float(a.im));
-  v.b = __floats2half2_rn(float(b.re), float(b.im));
-  *reinterpret_cast<Half2x2*>(p) = v;
-}
-
 // A spinor field of one parity, seen as two half-spinor fields: h = 0 holds spins
 // 0-1 (the P+ = (1+gamma_t)/2 subspace in the Dirac-Pauli basis), h = 1 spins 2-3.
-// Each half is 6 components [6][stride] (component = spin_in_half*3 + colour, paired as
-// above for FP32 / FP16); for FP16,
-// nrm[h] holds one FP32 scale per site.  The two halves may live in different
-// buffers, so a field can be assembled from the halves of two others.
+// Each half is 6 components [6][stride] (component = spin_in_half*3 + colour, paired for
+// FP32), or for FP16 the two planes of HalfRaw (7 four-byte units per site).  The two halves
+// may live in different buffers, so a field can be assembled from the halves of two others.
+template <typename S> TP_HD constexpr int half_units() { return sizeof(S) == 4 ? 7 : 6; }
 template <typename S>
 struct SpinorF {
   S* p[2];
-  float* nrm[2];
   int64_t stride;
 };
-// Field r of a batch of fields allocated back to back (24 planes of `stride` sites and 4
-// scale planes apart): the right-hand sides of a batched solve share one launch.
+// Field r of a batch of fields allocated back to back: the right-hand sides of a batched solve
+// share one launch.
 template <typename S> TP_DEV SpinorF<S> rhs_view(SpinorF<S> f, uint32_t r) {
-  const int64_t e = (int64_t)r * 24 * f.stride, n = (int64_t)r * 4 * f.stride;
+  const int64_t e = (int64_t)r * (4 * half_units<S>()) * f.stride;
   if (f.p[0]) f.p[0] += e;
   if (f.p[1]) f.p[1] += e;
-  if (f.nrm[0]) f.nrm[0] += n;
-  if (f.nrm[1]) f.nrm[1] += n;
   return f;
 }
 
@@ -156,86 +223,61 @@ template <typename T> TP_DEV T* at(T* plane, uint32_t i) {
   return reinterpret_cast<T*>(reinterpret_cast<char*>(plane) + uint32_t(i * uint32_t(sizeof(T))));
 }
 
-template <typename S, typename R = typename Prec<S>::R>
-TP_DEV void load_half(const SpinorF<S>& f, int h, uint32_t i, cx<R>* v) {
-  const S* b = f.p[h];
-  if constexpr (paired<S>()) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) ld2<R, S>(at(b + (int64_t)(2 * q) * f.stride, 2 * i), v[2 * q], v[2 * q + 1]);
-  } else {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = ld<R, S>(at(b + (int64_t)c * f.stride, i));
-  }
-  if constexpr (Prec<S>::half) {
-    R s = *at(f.nrm[h], i);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = s * v[c];
-  }
+// Six values of half h at site i, with 32-bit offsets from uniform plane bases, or with a 64-bit
+// site index and 64-bit addresses (the line kernels, whose register budget is better spent
+// elsewhere than on uniform plane bases).
+template <typename S> TP_DEV const S* plane_at(const S* plane, uint32_t i) { return at(plane, i); }
+template <typename S> TP_DEV const S* plane_at(const S* plane, int64_t i) { return plane + i; }
+template <typename S> TP_DEV S* plane_at(S* plane, uint32_t i) { return at(plane, i); }
+template <typename S> TP_DEV S* plane_at(S* plane, int64_t i) { return plane + i; }
+
+template <bool NT, typename I> TP_DEV void load_half_raw(HalfRaw& r, const SpinorF<__half2>& f, int h, I i) {
+  const __half2* b = f.p[h];
+  ld_half_raw<NT>(r, plane_at(b, I(4 * i)), plane_at(b + 4 * f.stride, I(3 * i)));
 }
 
-template <typename S, typename R = typename Prec<S>::R>
-TP_DEV void store_half(const SpinorF<S>& f, int h, uint32_t i, const cx<R>* v) {
-  S* b = f.p[h];
+template <bool NT, typename S, typename R, typename I>
+TP_DEV void load_half_as(const SpinorF<S>& f, int h, I i, cx<R>* v) {
+  const S* b = f.p[h];
   if constexpr (Prec<S>::half) {
-    R m = R(0);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) m = fmaxf(m, fmaxf(fabsf(v[c].re), fabsf(v[c].im)));
-    // below the smallest normal FP32 value 1/m would overflow (a point source decaying as
-    // mu^-t along a long line gets there): such a half spinor is stored as zero.  A NaN
-    // fails the comparison and propagates.
-    if (m < R(1.17549435e-38f)) m = R(0);
-    R inv = m > R(0) ? R(1) / m : R(0);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) st2(at(b + (int64_t)(2 * q) * f.stride, 2 * i), inv * v[2 * q], inv * v[2 * q + 1]);
-    *at(f.nrm[h], i) = m;
+    HalfRaw r;
+    load_half_raw<NT>(r, f, h, i);
+    r.unpack(v);
   } else if constexpr (paired<S>()) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) st2(at(b + (int64_t)(2 * q) * f.stride, 2 * i), v[2 * q], v[2 * q + 1]);
+    for (int q = 0; q < 3; ++q) {
+      const float4 e = ld_vec<NT>(reinterpret_cast<const float4*>(plane_at(b + (int64_t)(2 * q) * f.stride, I(2 * i))));
+      v[2 * q] = {e.x, e.y};
+      v[2 * q + 1] = {e.z, e.w};
+    }
   } else {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) st(at(b + (int64_t)c * f.stride, i), v[c]);
+    for (int c = 0; c < 6; ++c) {
+      const S e = ld_vec<NT>(plane_at(b + (int64_t)c * f.stride, i));
+      v[c] = {R(e.x), R(e.y)};
+    }
   }
+}
+template <typename S, typename R = typename Prec<S>::R, typename I>
+TP_DEV void load_half(const SpinorF<S>& f, int h, I i, cx<R>* v) {
+  load_half_as<false, S, R, I>(f, h, i, v);
+}
+template <typename S, typename R = typename Prec<S>::R, typename I>
+TP_DEV void nt_load_half(const SpinorF<S>& f, int h, I i, cx<R>* v) {
+  load_half_as<true, S, R, I>(f, h, i, v);
 }
 
-// The same with a 64-bit site index and 64-bit addresses (the line kernels, whose
-// register budget is better spent elsewhere than on uniform plane bases).
-template <typename S, typename R = typename Prec<S>::R>
-TP_DEV void load_half(const SpinorF<S>& f, int h, int64_t i, cx<R>* v) {
-  const S* b = f.p[h];
-  if constexpr (paired<S>()) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) ld2<R, S>(b + (int64_t)(2 * q) * f.stride + 2 * i, v[2 * q], v[2 * q + 1]);
-  } else {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = ld<R, S>(b + (int64_t)c * f.stride + i);
-  }
-  if constexpr (Prec<S>::half) {
-    R s = f.nrm[h][i];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = s * v[c];
-  }
-}
-template <typename S, typename R = typename Prec<S>::R>
-TP_DEV void store_half(const SpinorF<S>& f, int h, int64_t i, const cx<R>* v) {
+template <typename S, typename R = typename Prec<S>::R, typename I>
+TP_DEV void store_half(const SpinorF<S>& f, int h, I i, const cx<R>* v) {
   S* b = f.p[h];
   if constexpr (Prec<S>::half) {
-    R m = R(0);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) m = fmaxf(m, fmaxf(fabsf(v[c].re), fabsf(v[c].im)));
-    // below the smallest normal FP32 value 1/m would overflow (a point source decaying as
-    // mu^-t along a long line gets there): such a half spinor is stored as zero.  A NaN
-    // fails the comparison and propagates.
-    if (m < R(1.17549435e-38f)) m = R(0);
-    R inv = m > R(0) ? R(1) / m : R(0);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) st2(b + (int64_t)(2 * q) * f.stride + 2 * i, inv * v[2 * q], inv * v[2 * q + 1]);
-    f.nrm[h][i] = m;
+    st_half_raw(half_raw_of(v), plane_at(b, I(4 * i)), plane_at(b + 4 * f.stride, I(3 * i)));
   } else if constexpr (paired<S>()) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) st2(b + (int64_t)(2 * q) * f.stride + 2 * i, v[2 * q], v[2 * q + 1]);
+    for (int q = 0; q < 3; ++q) st2(plane_at(b + (int64_t)(2 * q) * f.stride, I(2 * i)), v[2 * q], v[2 * q + 1]);
   } else {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) st(b + (int64_t)c * f.stride + i, v[c]);
+    for (int c = 0; c < 6; ++c) st(plane_at(b + (int64_t)c * f.stride, i), v[c]);
   }
 }
 
@@ -265,12 +307,31 @@ template <typename R> TP_DEV void su3_third_row(su3<R>& u) {
   u.e[7] = conj(cmul(a[2], b[0]) - cmul(a[0], b[2]));
   u.e[8] = conj(cmul(a[0], b[1]) - cmul(a[1], b[0]));
 }
+// The first ROWS rows of an FP16 link (components 0-5 or 0-7 as pairs).
+template <int NP> TP_DEV void load_link_raw(Half2x2* lk, const LinkF<__half2>& f, uint32_t i) {
+  const Half2x4 v = *reinterpret_cast<const Half2x4*>(at(f.p, 4 * i));
+  lk[0] = v.a;
+  lk[1] = v.b;
+#pragma unroll
+  for (int q = 2; q < NP; ++q) lk[q] = *reinterpret_cast<const Half2x2*>(at(f.p + (int64_t)(2 * q) * f.stride, 2 * i));
+}
 // ROWS = 3 reads all nine entries; ROWS = 2 reads the first two rows of an SU(3) link and
 // rebuilds the third.
 template <typename R, typename L, int ROWS = 3>
 TP_DEV su3<R> load_su3(const LinkF<L>& f, uint32_t i) {
   su3<R> u;
-  if constexpr (paired<L>()) {
+  if constexpr (sizeof(L) == 4) {
+    constexpr int np = ROWS == 2 ? 3 : 4;
+    Half2x2 lk[np];
+    load_link_raw<np>(lk, f, i);
+#pragma unroll
+    for (int q = 0; q < np; ++q) {
+      const float2 fa = __half22float2(lk[q].a), fb = __half22float2(lk[q].b);
+      u.e[2 * q] = {fa.x, fa.y};
+      u.e[2 * q + 1] = {fb.x, fb.y};
+    }
+    if constexpr (ROWS == 3) u.e[8] = ld<R, L>(at(f.p + (int64_t)8 * f.stride, i));
+  } else if constexpr (paired<L>()) {
     constexpr int npair = ROWS == 2 ? 3 : 4;
 #pragma unroll
     for (int q = 0; q < npair; ++q) ld2<R, L>(at(f.p + (int64_t)(2 * q) * f.stride, 2 * i), u.e[2 * q], u.e[2 * q + 1]);
@@ -365,25 +426,28 @@ TP_DEV void herm6_from_slots(const cx<R>* sl, const cx<R>* v, cx<R>* out) {
   }
 }
 
-// The 18 slots of the block whose planes start at `base` (an even component index).
-template <typename R, typename L>
-TP_DEV void herm6_slots(const L* base, int64_t stride, uint32_t i, cx<R>* sl) {
-  if constexpr (paired<L>()) {
+// The 18 slots of the block whose planes start at `base`.
+template <typename R, typename L, typename I>
+TP_DEV void herm6_slots(const L* base, int64_t stride, I i, cx<R>* sl) {
+  if constexpr (sizeof(L) == 4) {
+    auto two = [](const Half2x2& h, cx<R>* o) {
+      const float2 fa = __half22float2(h.a), fb = __half22float2(h.b);
+      o[0] = {fa.x, fa.y};
+      o[1] = {fb.x, fb.y};
+    };
 #pragma unroll
-    for (int q = 0; q < 9; ++q) ld2<R, L>(at(base + (int64_t)(2 * q) * stride, 2 * i), sl[2 * q], sl[2 * q + 1]);
+    for (int q = 0; q < 4; ++q) {
+      const Half2x4 v = *reinterpret_cast<const Half2x4*>(plane_at(base + (int64_t)(4 * q) * stride, I(4 * i)));
+      two(v.a, sl + 4 * q);
+      two(v.b, sl + 4 * q + 2);
+    }
+    two(*reinterpret_cast<const Half2x2*>(plane_at(base + (int64_t)16 * stride, I(2 * i))), sl + 16);
+  } else if constexpr (paired<L>()) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) ld2<R, L>(plane_at(base + (int64_t)(2 * q) * stride, I(2 * i)), sl[2 * q], sl[2 * q + 1]);
   } else {
 #pragma unroll
-    for (int k = 0; k < 18; ++k) sl[k] = ld<R, L>(at(base + (int64_t)k * stride, i));
-  }
-}
-template <typename R, typename L>
-TP_DEV void herm6_slots(const L* base, int64_t stride, int64_t i, cx<R>* sl) {
-  if constexpr (paired<L>()) {
-#pragma unroll
-    for (int q = 0; q < 9; ++q) ld2<R, L>(base + (int64_t)(2 * q) * stride + 2 * i, sl[2 * q], sl[2 * q + 1]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 18; ++k) sl[k] = ld<R, L>(base + (int64_t)k * stride + i);
+    for (int k = 0; k < 18; ++k) sl[k] = ld<R, L>(plane_at(base + (int64_t)k * stride, i));
   }
 }
 

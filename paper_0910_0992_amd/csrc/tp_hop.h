@@ -51,26 +51,17 @@ TP_DEV void hop_dir(const SpinorF<S>& nb, const LinkF<Lt>& u_fwd, uint32_t i_fwd
 }
 
 // FP16 storage, two-row links: the operands of one projected hop in storage form, i.e. the
-// neighbour's two half spinors (three 8-byte pairs of FP16 complex values each, and their FP32
-// scales) and the first two rows of the link (three pairs).
+// neighbour's two half spinors and the first two rows of the link (six loads).
 struct HopRawH {
-  Half2x2 sp[2][3];
-  float sc[2];
+  HalfRaw sp[2];
   Half2x2 lk[3];
 };
 
 TP_DEV void hop_raw_load(HopRawH& r, const SpinorF<__half2>& nb, uint32_t j,
                          const LinkF<__half2>& u, uint32_t il) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      r.sp[h][q] = *reinterpret_cast<const Half2x2*>(at(nb.p[h] + (int64_t)(2 * q) * nb.stride, 2 * j));
-    r.sc[h] = *at(nb.nrm[h], j);
-  }
-#pragma unroll
-  for (int q = 0; q < 3; ++q)
-    r.lk[q] = *reinterpret_cast<const Half2x2*>(at(u.p + (int64_t)(2 * q) * u.stride, 2 * il));
+  for (int h = 0; h < 2; ++h) load_half_raw<false>(r.sp[h], nb, h, j);
+  load_link_raw<3>(r.lk, u, il);
 }
 
 // The same arithmetic as hop_dir's forward (FWD) or backward half, from operands in storage form.
@@ -78,13 +69,7 @@ template <int K, bool FWD>
 TP_DEV void hop_raw_apply(const HopRawH& r, float c, cx<float>* out) {
   cx<float> psi[12], h[6], w[6];
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float2 a = __half22float2(r.sp[hh][q].a), b = __half22float2(r.sp[hh][q].b);
-      psi[6 * hh + 2 * q] = r.sc[hh] * cx<float>{a.x, a.y};
-      psi[6 * hh + 2 * q + 1] = r.sc[hh] * cx<float>{b.x, b.y};
-    }
+  for (int hh = 0; hh < 2; ++hh) r.sp[hh].unpack(psi + 6 * hh);
   su3<float> U;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {

@@ -54,35 +54,33 @@ enum KernelId {
 extern const char* const kKernelNames[KID_COUNT];
 
 // ---------------------------------------------------------------- internal fields
-// A spinor field in an internal layout (p3 or p4), both parities:
-// data [2 parity][12 component][V2] of the storage type of `prec`,
-// nrm [2 parity][2 half][V2] FP32 scales for TP_F16N (else null).
+// A spinor field in an internal layout (p3 or p4), both parities: [2 parity][2 half] planes of
+// half spinors, 6 V2 elements of the storage type of `prec` each (TP_F16N: 7 V2 four-byte units,
+// six complex values and an FP32 scale per site; see HalfRaw).
 // A batch of nr such fields is one allocation of nr consecutive fields (kernels offset by
 // the right-hand-side index, see rhs_view); view(r) is field r alone.
 struct Field {
   int prec = TP_F64;
   void* data = nullptr;
-  float* nrm = nullptr;
   int64_t V2 = 0;
   int nr = 1;
   bool owned = false;
 
-  size_t elem_bytes() const { return prec == TP_F64 ? 16 : (prec == TP_F32 ? 8 : 4); }
+  // bytes of one half spinor of a site
+  static size_t half_bytes(int prec) { return prec == TP_F64 ? 96 : (prec == TP_F32 ? 48 : 28); }
   template <typename S>
   SpinorF<S> par(int p) const {
-    S* b = static_cast<S*>(data) + (int64_t)p * 12 * V2;
+    const int64_t h = (int64_t)half_units<S>() * V2;
+    S* b = static_cast<S*>(data) + (int64_t)p * 2 * h;
     SpinorF<S> f;
     f.p[0] = b;
-    f.p[1] = b + 6 * V2;
-    f.nrm[0] = nrm ? nrm + (int64_t)(2 * p) * V2 : nullptr;
-    f.nrm[1] = nrm ? nrm + (int64_t)(2 * p + 1) * V2 : nullptr;
+    f.p[1] = b + h;
     f.stride = V2;
     return f;
   }
   Field view(int r) const {
     Field f = *this;
-    f.data = static_cast<char*>(data) + (size_t)r * 24 * V2 * elem_bytes();
-    f.nrm = nrm ? nrm + (int64_t)r * 4 * V2 : nullptr;
+    f.data = static_cast<char*>(data) + (size_t)r * 4 * half_bytes(prec) * V2;
     f.nr = 1;
     f.owned = false;
     return f;
