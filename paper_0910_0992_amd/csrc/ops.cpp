@@ -60,7 +60,6 @@ Field& arena_get(tp_op op, int prec, int slot, int nr) {
   f.V2 = lat.V2;
   f.nr = nr;
   f.data = op->arena + op->arena_top;
-  f.owned = false;
   op->arena_top += need;
   auto& a = op->arena_slots[op->arena_n++];
   a.prec = prec;

@@ -62,9 +62,9 @@ extern const char* const kKernelNames[KID_COUNT];
 struct Field {
   int prec = TP_F64;
   void* data = nullptr;
+  void* base = nullptr;  // the allocation of a field that owns one (data lies inside it)
   int64_t V2 = 0;
   int nr = 1;
-  bool owned = false;
 
   // bytes of one half spinor of a site
   static size_t half_bytes(int prec) { return prec == TP_F64 ? 96 : (prec == TP_F32 ? 48 : 28); }
@@ -82,7 +82,7 @@ struct Field {
     Field f = *this;
     f.data = static_cast<char*>(data) + (size_t)r * 4 * half_bytes(prec) * V2;
     f.nr = 1;
-    f.owned = false;
+    f.base = nullptr;
     return f;
   }
 };
@@ -127,6 +127,7 @@ struct tp_ctx_s {
   void* alloc_user = nullptr;
   std::unordered_map<void*, size_t> live;
   size_t live_bytes = 0;
+  size_t fields_made = 0;  // large fields allocated so far (their start offsets differ)
   int nchildren = 0;  // gauge fields created from this context and not yet destroyed
   // device address of the library's fixed scratch array on this context's device
   // (tp_apply_prec_noalloc)
