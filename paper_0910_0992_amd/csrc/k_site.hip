@@ -10,18 +10,24 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Order in which the blocks of a one-block-per-chunk launch visit the tiles.  Workgroups go to
-// the 8 XCDs (each with its own L2) in turn, so block b runs on XCD b % 8.  A tile of 4 lines
-// spans Q = Lt / 64 blocks; XCD x takes the time range x % Q of the tiles in part x / Q of a
-// z-blocked tile sequence (x fastest, then z inside blocks of BZ planes, then y, then the z
-// block), so that the tiles holding a site's x, y and z neighbours were visited by the same
-// XCD 1, TX*BZ and TX blocks earlier.  off = identity.
+// Order in which the workgroups visit the chunks of 256 sites and the right-hand sides.
+// Workgroups go to the 8 XCDs (each with its own L2) in turn, so workgroup b runs on XCD b % 8.
+//   tiles: a launch of one workgroup per chunk whose chunks are whole parts of the tiles of 4
+//     lines (Q = Lt / 64 chunks each): XCD x takes the time range x % Q of the tiles in part
+//     x / Q of a z-blocked tile sequence (x fastest, then z inside blocks of BZ planes, then y,
+//     then the z block), so that the tiles holding a site's x, y and z neighbours were visited by
+//     the same XCD 1, TX*BZ and TX workgroups earlier;
+//   parts: each XCD takes one contiguous part of the chunks, in memory order, and every
+//     right-hand side of a chunk: y and z neighbours are then in its L2 as long as it holds the
+//     sites of one z plane;
+//   plain: in turn.
+enum { kOrderPlain = 0, kOrderTiles = 1, kOrderParts = 2 };
 struct TileOrder {
   uint32_t Q, TX, Ly, BZ, per_part;
-  int on;
+  int mode;
 };
 
-TP_DEV uint32_t ordered_block(const TileOrder& o, uint32_t b) {
+TP_DEV uint32_t tile_block(const TileOrder& o, uint32_t b) {
   const uint32_t x = b & 7u, n = b >> 3;
   const uint32_t q = (x / o.Q) * o.per_part + n;
   const uint32_t tx = q % o.TX;
@@ -32,12 +38,22 @@ TP_DEV uint32_t ordered_block(const TileOrder& o, uint32_t b) {
   const uint32_t tile = tx + o.TX * (y + o.Ly * (zb * o.BZ + zi));
   return tile * o.Q + x % o.Q;
 }
+// The b-th of n workgroups when each XCD takes a contiguous part.
+TP_DEV uint32_t xcd_block(uint32_t b, uint32_t n) {
+  const uint32_t x = b & 7u, per = n >> 3, rest = n & 7u;
+  return x * per + (x < rest ? x : rest) + (b >> 3);
+}
 
-// The XCD-aware order where the launch shape allows it (one block per chunk of 256 sites,
-// whole tiles per block group, tiles inside x rows), else off.
-TileOrder tile_order(const Lattice& L, int64_t nblocks, int nr, bool half) {
-  TileOrder o{1, 1, 1, 1, 0, 0};
+// Measured rules.  Tiles, against plain: 4-19% faster hops in F32 and F16N at 16^3x128, 24^3x128
+// and (F32) 32^3x256, but 2-5% slower for FP16 storage with four chunks per tile (256-slice
+// lines), which keeps the plain order.  Parts, where the launch has no whole tiles, against plain:
+// F32 hop at 14x14x12x107 27.6 -> 16.3 us, at 24^3x120 (3.3 MB of neighbour spinors a plane) 125 ->
+// 99, FP64 residual at 20x20x22x46 (1.8 MB) 123 -> 108, but at 24^3x120 (6.6 MB) 411 -> 433 and F16N
+// with 12 right-hand sides at 16^3x128 (11 MB) 117 -> 121: parts up to 6 MB a plane.
+TileOrder tile_order(const Lattice& L, int64_t nblocks, int nr, double spinor) {
+  TileOrder o{1, 1, 1, 1, 0, kOrderPlain};
   const Geom& g = L.g;
+  if (double(g.Lxh) * g.Ly * g.Lt * nr * spinor <= 6e6) o.mode = kOrderParts;
   if (nr != 1 || int64_t(nblocks) * kBlock != g.V2) return o;
   if (g.Lt % 64 || (8 % (g.Lt / 64)) || g.Lxh % kTile) return o;
   const uint32_t Q = uint32_t(g.Lt / 64), tiles = uint32_t(g.Vs2 / kTile);
@@ -47,10 +63,7 @@ TileOrder tile_order(const Lattice& L, int64_t nblocks, int nr, bool half) {
   o.Ly = uint32_t(g.Ly);
   o.BZ = g.Lz % 8 == 0 ? 8u : g.Lz % 4 == 0 ? 4u : g.Lz % 2 == 0 ? 2u : 1u;
   o.per_part = tiles * Q / 8;
-  o.on = 1;
-  // measured: with FP16 storage and four blocks per tile (256-slice lines) the identity
-  // order was 2.7% faster; everywhere else this order was 4-19% faster
-  o.on = !(half && Q >= 4);
+  o.mode = spinor < 60 && Q >= 4 ? kOrderPlain : kOrderTiles;
   return o;
 }
 
@@ -64,7 +77,7 @@ struct SiteArgsP3 {
   double c_mu, c_A, c_t, c_s, c_in;
   Geom g;
   int par;  // output parity of this launch
-  int nr;   // right-hand sides: block b works on field b % nr of each batch
+  int nr;   // right-hand sides
   double* partial;
   TileOrder ord;
 };
@@ -77,10 +90,13 @@ __global__ void __launch_bounds__(kBlock) k_site_p3(SiteArgsP3<S> a) {
   __shared__ double red[kBlock / 64];
   double acc = 0.0;
   const int p = a.par;  // one parity per launch: every field plane address is uniform
-  const uint32_t nr = uint32_t(a.nr), rhs = blockIdx.x % nr, blk = blockIdx.x / nr, nblk = gridDim.x / nr;
+  const uint32_t nr = uint32_t(a.nr), nblk = gridDim.x / nr;
+  const uint32_t id = a.ord.mode == kOrderTiles   ? tile_block(a.ord, blockIdx.x)
+                      : a.ord.mode == kOrderParts ? xcd_block(blockIdx.x, gridDim.x)
+                                                  : blockIdx.x;
+  const uint32_t rhs = id % nr, first = id / nr;
   const SpinorF<S> self = rhs_view(a.self[p], rhs), nbf = rhs_view(a.nb[p], rhs);
   const SpinorF<S> in2 = rhs_view(a.in2[p], rhs), dst = rhs_view(a.dst[p], rhs);
-  const uint32_t first = a.ord.on ? ordered_block(a.ord, blk) : blk;
   for (uint32_t i = first * blockDim.x + threadIdx.x; i < uint32_t(a.g.V2); i += nblk * blockDim.x) {
     int t, s;
     p3_ts32(a.g, i, t, s);
@@ -291,7 +307,7 @@ int site_t(tp_op op, const SiteIO& io, Field& dst, SiteCoef cf, int ck, int par0
   if (norm && a.nr != 1) TP_THROW(TP_EINVAL, "a fused norm needs a single right-hand side");
   int64_t nb = (L.V2 + kBlock - 1) / kBlock;
   if (norm) nb = std::min<int64_t>(nb, kRedBlocks / 2);
-  a.ord = tile_order(L, nb, a.nr, Prec<S>::half);
+  a.ord = tile_order(L, nb, a.nr, 2.0 * Field::half_bytes(dst.prec));
   bool dt = cf.c_t != 0.0, ds = cf.c_s != 0.0;
   bool i2 = in2 != nullptr;
   // spatial hops read SU(3) links as two rows (FP64: only links SU(3) to 1e-13)
