@@ -777,12 +777,36 @@ tp_status tp_op_mass(tp_op op, double* mu) {
   });
 }
 
+// FP64 applies that work on the caller's canonical fields directly (k_canon.hip): the same
+// argument checks as apply_wrap.  Returns false, having done nothing, for the calls that go through
+// the internal layout: reduced precisions, and fields that overlap (each input is then packed
+// before any output is written).
+static bool canon_direct(tp_op op, int32_t prec, const void* dst, const void* src) {
+  if (!op || !dst || !src || prec != TP_F64) return false;
+  const uintptr_t d = reinterpret_cast<uintptr_t>(dst), s = reinterpret_cast<uintptr_t>(src);
+  const size_t bytes = size_t(op->g->ctx->lat.V) * 12 * sizeof(double2);
+  return d >= s + bytes || s >= d + bytes;
+}
+static tp_status apply_canon(tp_op op, void* dst, const void* src, bool g5, SiteCoef cf, const double2* clov) {
+  return guard([&] {
+    set_device(op->g->ctx);
+    launch_site_canon(op, static_cast<const double2*>(src), static_cast<double2*>(dst), g5, cf, clov);
+  });
+}
+static tp_status canon_M(tp_op op, void* dst, const void* src, bool dagger) {
+  return apply_canon(op, dst, src, dagger, SiteCoef{op->mu, 1.0, -1.0, -1.0 / op->gf, 0.0},
+                     op->c ? op->c->a4_d : nullptr);
+}
+
 tp_status tp_apply_M(tp_op op, int32_t prec, void* dst, const void* src, int32_t dagger) {
+  if (canon_direct(op, prec, dst, src)) return canon_M(op, dst, src, dagger != 0);
   return apply_wrap(op, prec, dst, src, false, dagger != 0,
                     [&](Field& a, Field& b) { op_apply_M(op, prec, a, b, false); });
 }
 
 tp_status tp_apply_Ds(tp_op op, int32_t prec, void* dst, const void* src) {
+  if (canon_direct(op, prec, dst, src))
+    return apply_canon(op, dst, src, false, SiteCoef{0.0, 0.0, 0.0, 1.0, 0.0}, nullptr);
   return apply_wrap(op, prec, dst, src, false, false, [&](Field& a, Field& b) {
     SiteCoef cf{0.0, 0.0, 0.0, 1.0, 0.0};
     launch_site_p3(op, prec, a, b, nullptr, cf, 0, 0, 2, false);
@@ -790,8 +814,12 @@ tp_status tp_apply_Ds(tp_op op, int32_t prec, void* dst, const void* src) {
 }
 
 tp_status tp_apply_clover(tp_op op, int32_t prec, void* dst, const void* src, int32_t plus_mu) {
+  const int kind = plus_mu == 0 ? 1 : (plus_mu > 0 ? 2 : 3);
+  if (canon_direct(op, prec, dst, src) && !(kind == 1 && !op->c)) {
+    const double2* blocks = kind == 1 ? op->c->a4_d : (kind == 2 ? op->a4_mu : op->a4_inv);
+    return apply_canon(op, dst, src, false, SiteCoef{0.0, 1.0, 0.0, 0.0, 0.0}, blocks);
+  }
   return apply_wrap(op, prec, dst, src, false, false, [&](Field& a, Field& b) {
-    int kind = plus_mu == 0 ? 1 : (plus_mu > 0 ? 2 : 3);
     if (kind == 1 && !op->c) {
       blas(op->g->ctx, B_ZERO, 0, 2, {nullptr, &b});
       return;
@@ -807,19 +835,25 @@ static void line_both(tp_op op, int prec, int mode, Field& a, Field& b) {
   for (int p = 0; p < 2; ++p) launch_line(op, prec, mode, p, io, b);
 }
 
+static tp_status line_apply(tp_op op, int prec, int mode, void* dst, const void* src) {
+  if (canon_direct(op, prec, dst, src))
+    return guard([&] {
+      set_device(op->g->ctx);
+      launch_line_canon(op, mode, static_cast<const double2*>(src), static_cast<double2*>(dst));
+    });
+  return apply_wrap(op, prec, dst, src, false, false, [&](Field& a, Field& b) { line_both(op, prec, mode, a, b); });
+}
+
 tp_status tp_apply_Tinv(tp_op op, int32_t prec, void* dst, const void* src, int32_t dagger) {
-  return apply_wrap(op, prec, dst, src, false, false,
-                    [&](Field& a, Field& b) { line_both(op, prec, dagger ? LM_TDINV : LM_TINV, a, b); });
+  return line_apply(op, prec, dagger ? LM_TDINV : LM_TINV, dst, src);
 }
 
 tp_status tp_apply_CL(tp_op op, int32_t prec, void* dst, const void* src) {
-  return apply_wrap(op, prec, dst, src, false, false,
-                    [&](Field& a, Field& b) { line_both(op, prec, LM_CL, a, b); });
+  return line_apply(op, prec, LM_CL, dst, src);
 }
 
 tp_status tp_apply_CR(tp_op op, int32_t prec, void* dst, const void* src) {
-  return apply_wrap(op, prec, dst, src, false, false,
-                    [&](Field& a, Field& b) { line_both(op, prec, LM_CR, a, b); });
+  return line_apply(op, prec, LM_CR, dst, src);
 }
 
 tp_status tp_apply_prec(tp_op op, int32_t scheme, int32_t prec, void* dst, const void* src,
@@ -827,6 +861,10 @@ tp_status tp_apply_prec(tp_op op, int32_t scheme, int32_t prec, void* dst, const
   return guard([&] {
     check_scheme(scheme);
     check_scheme_prec(scheme, prec);
+    if (scheme == TP_UNPREC && canon_direct(op, prec, dst, src)) {
+      if (tp_status st = canon_M(op, dst, src, dagger != 0)) TP_THROW(st, g_last_error);
+      return;
+    }
     // dagger: gamma5 on the way in and out around N (Mt^dagger = gamma5 N gamma5)
     tp_status s = apply_wrap(op, prec, dst, src, scheme_layout4(scheme), dagger != 0,
                              [&](Field& a, Field& b) {
@@ -886,6 +924,10 @@ tp_status tp_prepare_source(tp_op op, int32_t scheme, int32_t prec, void* et, co
   return guard([&] {
     check_scheme(scheme);
     check_scheme_prec(scheme, prec);
+    if (scheme == TP_TEMPORAL && canon_direct(op, prec, et, eta)) {
+      if (tp_status st = line_apply(op, prec, LM_CL, et, eta)) TP_THROW(st, g_last_error);
+      return;
+    }
     tp_status s = apply_wrap(op, prec, et, eta, scheme_layout4(scheme), false,
                              [&](Field& a, Field& b) { op_prepare(op, scheme, prec, a, b); });
     if (s != TP_OK) TP_THROW(s, g_last_error);
@@ -896,6 +938,10 @@ tp_status tp_reconstruct(tp_op op, int32_t scheme, int32_t prec, void* x, const 
   return guard([&] {
     check_scheme(scheme);
     check_scheme_prec(scheme, prec);
+    if (scheme == TP_TEMPORAL && canon_direct(op, prec, x, y)) {
+      if (tp_status st = line_apply(op, prec, LM_CR, x, y)) TP_THROW(st, g_last_error);
+      return;
+    }
     tp_status s = apply_wrap(op, prec, x, y, scheme_layout4(scheme), false,
                              [&](Field& a, Field& b) { op_reconstruct(op, scheme, prec, a, b); });
     if (s != TP_OK) TP_THROW(s, g_last_error);

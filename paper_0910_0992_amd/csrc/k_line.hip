@@ -9,6 +9,8 @@ TP_DECL(f64)
 TP_DECL(f32)
 TP_DECL(f16)
 
+void line_canon_f64(tp_op, int, const double2*, double2*);
+
 #define TP_DISPATCH(prec, fn, ...)            \
   switch (prec) {                             \
     case TP_F64: fn##f64(__VA_ARGS__); break; \
@@ -29,6 +31,12 @@ void launch_line(tp_op op, int prec, int mode, int par, const LineIO& io, Field&
   const int kid = mode == LM_CR ? KID_SCAN_CR : (mode == LM_CL ? KID_SCAN_CL : KID_SCAN_OTHER);
   ProfScope ps(op->g->ctx, kid, double(L.V2) * per * dst.nr);
   TP_DISPATCH(prec, line_, op, mode, par, io, dst)
+}
+
+void launch_line_canon(tp_op op, int mode, const double2* src, double2* dst) {
+  const int kid = mode == LM_CR ? KID_SCAN_CR : (mode == LM_CL ? KID_SCAN_CL : KID_SCAN_OTHER);
+  ProfScope ps(op->g->ctx, kid, double(op->g->ctx->lat.V) * (2 * 192 + 144));
+  line_canon_f64(op, mode, src, dst);
 }
 
 void launch_ilu_mid(tp_op op, int prec, const Field& psi, const Field& u, Field& chi, Field& n) {

@@ -38,11 +38,6 @@ TP_DEV uint32_t tile_block(const TileOrder& o, uint32_t b) {
   const uint32_t tile = tx + o.TX * (y + o.Ly * (zb * o.BZ + zi));
   return tile * o.Q + x % o.Q;
 }
-// The b-th of n workgroups when each XCD takes a contiguous part.
-TP_DEV uint32_t xcd_block(uint32_t b, uint32_t n) {
-  const uint32_t x = b & 7u, per = n >> 3, rest = n & 7u;
-  return x * per + (x < rest ? x : rest) + (b >> 3);
-}
 
 // Measured rules.  Tiles, against plain: 4-19% faster hops in F32 and F16N at 16^3x128, 24^3x128
 // and (F32) 32^3x256, but 2-5% slower for FP16 storage with four chunks per tile (256-slice

@@ -473,6 +473,13 @@ TP_DEV void clover_apply(const L* cl, int64_t stride, I i, const cx<R>* psi, cx<
   for (int c = 0; c < 6; ++c) { out[c] = bp[c] + bm[c]; out[6 + c] = bm[c] - bp[c]; }
 }
 
+// ---- workgroup order ---------------------------------------------------------------------
+// Workgroups go to the 8 XCDs in turn; the b-th of n when each XCD takes a contiguous part.
+TP_DEV uint32_t xcd_block(uint32_t b, uint32_t n) {
+  const uint32_t x = b & 7u, per = n >> 3, rest = n & 7u;
+  return x * per + (x < rest ? x : rest) + (b >> 3);
+}
+
 // ---- lattice geometry ----------------------------------------------------------------------
 // p3 ("line") layout: parity p = (x+y+z)&1; spatial index s = (x + Lx*(y + Ly*z)) >> 1;
 // a time line (fixed s) stays inside one parity.  Lines are grouped in tiles of 4 and

@@ -264,6 +264,11 @@ int launch_site_p3(tp_op op, int prec, const Field& src, Field& dst, const Field
                    SiteCoef cf, int clover_kind /*0 none,1 A,2 (A+mu),3 (A+mu)^-1*/,
                    int par0, int npar, bool want_norm);
 
+// dst = c_mu psi + c_A A psi + c_t D_t psi + c_s D_s psi on canonical FP64 fields that do not
+// overlap, in the original frame, between two gamma5 when g5 (k_canon.hip).  clov: p4 blocks of the
+// clover term to apply (A, A + mu or its inverse), or null.
+void launch_site_canon(tp_op op, const double2* src, double2* dst, bool g5, SiteCoef cf, const double2* clov);
+
 // 4D Schur pieces on the p4 layout (FP64 and FP32 storage).
 //   mode 0: dst_e = (A+mu)^-1 (c_h D_w^eo src_o)              [clover after hop]
 //   mode 1: dst_o = (A+mu) src_o + c_h D_w^oe t_e             [clover on self]
@@ -286,6 +291,8 @@ struct LineIO {
   bool pass = true;
 };
 void launch_line(tp_op op, int prec, int mode, int par, const LineIO& io, Field& dst);
+// dst = MODE(src) on both parities of canonical FP64 fields that do not overlap (not LM_CRCL).
+void launch_line_canon(tp_op op, int mode, const double2* src, double2* dst);
 // Fused middle step of the 3D ILU operator (even parity): from psi_e and
 // u = D_s^eo a_o / gamma_f, chi_e = psi_e + C_L y and n_e = C_R C_L (y - u) with
 // y = A C_R (C_L u + psi_e).

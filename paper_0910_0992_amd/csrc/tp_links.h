@@ -53,8 +53,7 @@ struct SubSite {
 };
 inline unsigned sub_blocks(const Lattice& L) { return 2u * unsigned((L.Vs2 + 15) / 16) * unsigned((L.L[3] + 3) / 4); }
 TP_DEV SubSite sub_site(const Geom& g, int lane) {
-  const uint32_t n = gridDim.x, x = blockIdx.x & 7u, per = n >> 3, rest = n & 7u;
-  const uint32_t id = x * per + (x < rest ? x : rest) + (blockIdx.x >> 3);
+  const uint32_t id = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t blk = id >> 1, nsb = uint32_t(g.Vs2 + 15) / 16;
   const int s = int(blk % nsb) * 16 + (lane & 15), t = int(blk / nsb) * 4 + (lane >> 4);
   SubSite q;

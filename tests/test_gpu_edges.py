@@ -88,3 +88,49 @@ def test_links_and_plaquette(dims, host):
     assert abs(ps - (pl(0, 1) + pl(0, 2) + pl(1, 2)) / 3) < 1e-13
     assert abs(pt - (pl(0, 3) + pl(1, 3) + pl(2, 3)) / 3) < 1e-13
     g.close()
+
+
+# canonical FP64 applies: time extents around the line kernels' chunks (one, two and four slices a
+# thread; multiples of 16 and not), line counts that are no multiple of a workgroup's
+CANON_DIMS = SUB_DIMS + [(6, 10, 2, 45), (2, 4, 2, 128), (2, 2, 4, 130), (2, 2, 2, 256), (2, 2, 2, 260), (10, 6, 2, 16)]
+
+
+@pytest.mark.parametrize("dims", CANON_DIMS)
+@pytest.mark.parametrize("clover", [True, False])
+@pytest.mark.parametrize("cut", [0.0, 1e-3])
+def test_canonical_applies(dims, clover, cut):
+    """The FP64 applies that work on canonical fields directly, against the oracle and against the
+    FP64 path through the internal layout (which overlapping buffers take, as before)."""
+    U, o, g = _make(dims, cs=1.6 if clover else 0.0, ct=1.0 if clover else 0.0, bc=1 if dims[0] == 6 else -1)
+    eta = synth.make_source(dims, 2104)
+    t = torch.from_numpy(eta).cuda()
+    calls = {"Tinv": lambda v: g.apply_Tinv(v), "Tdinv": lambda v: g.apply_Tinv(v, dagger=True), "CL": g.apply_CL,
+             "CR": g.apply_CR, "prep": lambda v: g.prepare_source(v, "TEMPORAL"),
+             "rec": lambda v: g.reconstruct(v, "TEMPORAL")}
+    if cut == 0.0:
+        refs = {"Tinv": o.tmp.Tinv(eta), "Tdinv": o.tmp.Tdaginv(eta), "CL": o.tmp.CL(eta), "CR": o.tmp.CR(eta)}
+        refs.update(prep=refs["CL"], rec=refs["CR"])
+        for k, r in refs.items():
+            assert _rel(calls[k](t), r) < TOL64, k
+        assert _rel(g.apply_M(t), o.M(eta)) < TOL64
+        assert _rel(g.apply_M(t, dagger=True), o.Mdag(eta)) < TOL64
+        assert _rel(g.apply_prec(t, "UNPREC", dagger=True), o.Mdag(eta)) < TOL64
+        assert _rel(g.apply_Ds(t), o.Ds(eta)) < TOL64
+        for plus, f in ((1, o.Amu), (-1, o.Amu_inv)) + (((0, o.Aop),) if clover else ()):
+            assert _rel(g.apply_clover(t, "F64", plus), f(eta)) < TOL64
+    else:
+        g.set_cutoff(cut)
+    # overlapping buffers: dst starts one site behind src
+    n = eta.size
+    buf = torch.zeros(n + 12, dtype=torch.complex128, device="cuda")
+    import ctypes as C
+    L = g._lib
+    for name, fn in (("Tinv", lambda d, s: L.tp_apply_Tinv(g._op, 0, d, s, 0)), ("Tdinv", lambda d, s: L.tp_apply_Tinv(g._op, 0, d, s, 1)),
+                     ("CL", lambda d, s: L.tp_apply_CL(g._op, 0, d, s)), ("CR", lambda d, s: L.tp_apply_CR(g._op, 0, d, s))):
+        buf[:n] = t.reshape(-1)
+        assert fn(C.c_void_p(buf[12:].data_ptr()), C.c_void_p(buf.data_ptr())) == 0
+        assert _rel(calls[name](t).reshape(-1), buf[12:].cpu().numpy()) < TOL64, name
+    buf[:n] = t.reshape(-1)
+    assert L.tp_apply_M(g._op, 0, C.c_void_p(buf[12:].data_ptr()), C.c_void_p(buf.data_ptr()), 0) == 0
+    assert _rel(g.apply_M(t).reshape(-1), buf[12:].cpu().numpy()) < TOL64
+    g.close()
