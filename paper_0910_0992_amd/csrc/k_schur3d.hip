@@ -19,12 +19,15 @@
 // rows 6-11 of slice Lt-1.  T0 is factored once by block LU,
 //   S(0) = B(0),   S(t) = B(t) - P_+ S(t-1)^-1 P_-,
 // and a solve is a forward sweep w(t) = S(t)^-1 (eta(t) + P_+ w(t-1)) and a backward sweep
-// x(t) = w(t) + S(t)^-1 P_- x(t+1).  An apply is two such solves: the first only yields
-// W^dag T0^-1 eta.  K comes from twelve solves with the unit vectors as beta and eta = 0.
+// x(t) = w(t) + S(t)^-1 P_- x(t+1).  An apply is two such solves, the first of which only yields
+// W^dag T0^-1 eta, with what the second can take from the first (k_s3_solve).  K comes from twelve
+// solves with the unit vectors as beta and eta = 0.
 //
 // Storage per parity: S(t)^-1 for every site as [tile][t][column][row][line of the tile], so the
 // 48 lanes (row, line) of one wavefront that handle a tile read one column in a single
 // contiguous load (768 bytes in FP64).  K is [line][row][column].
+#include <type_traits>
+
 #include "tp_internal.h"
 
 namespace {
@@ -206,133 +209,288 @@ __device__ int64_t row_off(int r, int64_t V2, int64_t i) {
   return comp_off<T>(r < 6 ? r : r - 6, 6, V2, i);
 }
 
-// Operands of one sweep launch, per parity slot k = blockIdx.y (one or two parities).
-template <typename T>
-struct Sweep {
-  const T* in_up[2] = {};    // forward: eta (null: eta = 0); backward: w
-  const T* in_lo[2] = {};
-  T* out_up[2] = {};         // forward: w; backward: x (null: not stored)
-  T* out_lo[2] = {};
-  const T* base_up[2] = {};  // backward: x is stored as base - x when given
-  const T* base_lo[2] = {};
-  const T* sinv[2] = {};
-  const T* kmat[2] = {};     // forward: beta = K q per line when given
-  const T* q[2] = {};
-  T* qout[2] = {};           // backward: W^dag x per line when given
-  const double2* link_t[2] = {};  // FP64 planes [9][V2] of the parity's axial time links
-  int unit = -1;             // forward: beta = unit vector `unit` when >= 0
-};
+// Row ln.r of c(beta) = -V beta: P^dag beta_0..5 for rows 0-5 (of slice 0), P beta_6..11 for rows
+// 6-11 (of slice Lt-1); beta(k) is component k of the lane's line.
+template <typename R, typename F>
+__device__ cx<R> corner_term(const double2* __restrict__ link_t, const SweepLane& ln, int64_t V2, const Geom& g,
+                             F&& beta) {
+  const int64_t ib = p3_idx(g, g.Lt - 1, ln.s);
+  const int rr = ln.r < 6 ? ln.r : ln.r - 6;
+  const int sp = rr / 3, c3 = rr % 3;
+  cx<R> v = czero<R>();
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    if (ln.r < 6) {
+      const double2 u = link_t[(int64_t)(b * 3 + c3) * V2 + ib];  // (P^dag)_{ab} = conj(P_{ba})
+      v += cmulc(cx<R>{R(u.x), R(u.y)}, beta(sp * 3 + b));
+    } else {
+      const double2 u = link_t[(int64_t)(c3 * 3 + b) * V2 + ib];
+      v += cmul(cx<R>{R(u.x), R(u.y)}, beta(6 + sp * 3 + b));
+    }
+  }
+  return v;
+}
 
-// Forward sweep: w(t) = S(t)^-1 (eta(t) + P_+ w(t-1) + c(beta)(t)), storage T (double2:
-// FP64; float2: FP32 factors and spinors, FP32 arithmetic).  The corner term is K q when
-// kmat is given, the unit vector `unit` when unit >= 0, else absent.
-template <typename T>
-__global__ __launch_bounds__(64) void k_s3_forward(Sweep<T> a, int64_t V2, Geom g) {
-  using R = typename Prec<T>::R;
-  __shared__ cx<R> zb[4][12];
-  __shared__ cx<R> db[4][12];
+// The two sweeps of one set-up solve of T0 per line, whose right-hand side is the corner term of
+// unit vector `unit`: w(t) = S(t)^-1 (c(t) + P_+ w(t-1)) forward (w: work field), then
+// x(t) = w(t) + S(t)^-1 P_- x(t+1) backward, of which only W^dag x = (rows 0-5 of x(Lt-1), rows
+// 6-11 of x(0)) is kept.
+__global__ __launch_bounds__(64) void k_s3_unit(double2* w_up, double2* w_lo, const double2* __restrict__ sinv,
+                                                const double2* __restrict__ link_t, double2* qout, int unit,
+                                                int64_t V2, Geom g) {
+  __shared__ cx<double> zb[48];
   const SweepLane ln = sweep_lane();
-  const T* kmat = a.kmat[ln.k];
-  const bool corner = kmat != nullptr || a.unit >= 0;
-  if (ln.active && corner) {
-    cx<R> d = czero<R>();
-    if (kmat) {
-      const T* kr = kmat + (int64_t)ln.s * 144 + ln.r * 12;
-      const T* qs = a.q[ln.k] + (int64_t)ln.s * 12;
-#pragma unroll
-      for (int c = 0; c < 12; ++c) d += cmul(ld<R, T>(kr + c), ld<R, T>(qs + c));
-    } else if (ln.r == a.unit) {
-      d = cx<R>{R(1), R(0)};
-    }
-    db[ln.l][ln.r] = d;
-  }
-  __syncthreads();
-  // this lane's corner term: rows 0-5 at t = 0, rows 6-11 at t = Lt-1
-  cx<R> corr = czero<R>();
-  if (ln.active && corner) {
-    const double2* link_t = a.link_t[ln.k];
-    const int64_t ib = p3_idx(g, g.Lt - 1, ln.s);
-    const int rr = ln.r < 6 ? ln.r : ln.r - 6;
-    const int sp = rr / 3, c3 = rr % 3;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      if (ln.r < 6) {
-        double2 u = link_t[(int64_t)(b * 3 + c3) * V2 + ib];  // (P^dag)_{ab} = conj(P_{ba})
-        corr += cmulc(cx<R>{R(u.x), R(u.y)}, db[ln.l][sp * 3 + b]);
-      } else {
-        double2 u = link_t[(int64_t)(c3 * 3 + b) * V2 + ib];
-        corr += cmul(cx<R>{R(u.x), R(u.y)}, db[ln.l][6 + sp * 3 + b]);
-      }
-    }
-  }
-  const T* ep = ln.active && a.in_up[ln.k] ? (ln.r < 6 ? a.in_up[ln.k] : a.in_lo[ln.k]) : nullptr;
-  T* wp = ln.active ? (ln.r < 6 ? a.out_up[ln.k] : a.out_lo[ln.k]) : nullptr;
-  const T* sbase = a.sinv[ln.k] + (int64_t)ln.tile * g.Lt * 576 + ln.lane;
-  cx<R> wprev = czero<R>();
+  cx<double> corr = czero<double>();
+  if (ln.active) corr = corner_term<double>(link_t, ln, V2, g, [&](int k) {
+    return cx<double>{k == unit ? 1.0 : 0.0, 0.0};
+  });
+  double2* wp = ln.active ? (ln.r < 6 ? w_up : w_lo) : nullptr;
+  const double2* sbase = sinv + (int64_t)ln.tile * g.Lt * 576 + ln.lane;
+  cx<double> prev = czero<double>();
 #pragma unroll 1
   for (int t = 0; t < g.Lt; ++t) {
-    const int64_t i = p3_idx(g, t, ln.s);
     if (ln.active) {
-      cx<R> z = czero<R>();
-      if (ep) z = ld<R, T>(ep + row_off<T>(ln.r, V2, i));
+      cx<double> z = czero<double>();
       if (ln.r < 6) {
-        z += wprev;
+        z = prev;
         if (t == 0) z += corr;
       } else if (t == g.Lt - 1) {
-        z += corr;
+        z = corr;
       }
-      zb[ln.l][ln.r] = z;
+      zb[ln.lane] = z;
     }
     __syncthreads();
     if (ln.active) {
-      const T* sc = sbase + (int64_t)t * 576;
-      cx<R> w = czero<R>();
+      const double2* sc = sbase + (int64_t)t * 576;
+      cx<double> w = czero<double>();
 #pragma unroll
-      for (int c = 0; c < 12; ++c) w += cmul(ld<R, T>(sc + c * 48), zb[ln.l][c]);
-      st(wp + row_off<T>(ln.r, V2, i), w);
-      wprev = w;
+      for (int c = 0; c < 12; ++c) w += cmul(ld<double, double2>(sc + c * 48), zb[c * 4 + ln.l]);
+      st(wp + (int64_t)(ln.r % 6) * V2 + p3_idx(g, t, ln.s), w);
+      prev = w;
+    }
+    __syncthreads();
+  }
+#pragma unroll 1
+  for (int t = g.Lt - 1; t >= 0; --t) {
+    cx<double> x = czero<double>();
+    if (ln.active) {
+      x = ld<double, double2>(wp + (int64_t)(ln.r % 6) * V2 + p3_idx(g, t, ln.s));
+      if (t < g.Lt - 1) {
+        const double2* sc = sbase + (int64_t)t * 576;
+#pragma unroll
+        for (int c = 6; c < 12; ++c) x += cmul(ld<double, double2>(sc + c * 48), zb[c * 4 + ln.l]);
+      }
+    }
+    __syncthreads();  // every lane has read x(t+1)
+    if (ln.active) {
+      zb[ln.lane] = x;
+      if ((t == g.Lt - 1 && ln.r < 6) || (t == 0 && ln.r >= 6)) st(qout + (int64_t)ln.s * 12 + ln.r, x);
     }
     __syncthreads();
   }
 }
 
-// Backward sweep: x(t) = w(t) + S(t)^-1 P_- x(t+1).  out (optional) receives x, or base - x
-// when base is given; qout (optional) receives W^dag x = (rows 0-5 of x(Lt-1), rows 6-11
-// of x(0)) per line.
+// Orders LDS accesses between the lanes of a workgroup of one wavefront, whose LDS operations
+// execute in order: unlike a barrier it waits for nothing, least of all the loads ahead.
+TP_DEV void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Operands of a solve per parity slot k = blockIdx.y (one or two parities).
 template <typename T>
-__global__ __launch_bounds__(64) void k_s3_backward(Sweep<T> a, int64_t V2, Geom g) {
+struct Sweep {
+  const T* in_up[2] = {};  // eta
+  const T* in_lo[2] = {};
+  T* w_up[2] = {};         // work field
+  T* w_lo[2] = {};
+  T* out_up[2] = {};       // x, or base - x when base is given
+  T* out_lo[2] = {};
+  const T* base_up[2] = {};
+  const T* base_lo[2] = {};
+  const T* sinv[2] = {};
+  const T* kmat[2] = {};
+  const double2* link_t[2] = {};  // FP64 planes [9][V2] of the parity's axial time links
+};
+
+// x = T^-1 eta on one tile of 4 lines per wavefront, all four sweeps in one launch, storage T
+// (double2: FP64; float2: FP32 factors and spinors, FP32 arithmetic):
+//   1 forward   w(t) = S(t)^-1 (eta(t) + P_+ w(t-1))
+//   2 backward  y(t) = w_lo(t) + [S(t)^-1]_lo,lo y(t+1): only y(0) is wanted, so only the lower rows
+//               and columns are read; q = (w_up(Lt-1), y(0)) = W^dag T0^-1 eta, beta = K q
+//   3 forward   w += w', the solution of the same recurrence for the corner term of beta alone:
+//               w'(t) = S(t)^-1 P_+ w'(t-1) reads the upper columns
+//   4 backward  x(t) = w(t) + S(t)^-1 P_- x(t+1)
+// A step is a dependent chain (publish 12 values, twelve products, their sum), but the factors it
+// multiplies by are not: they are loaded several steps ahead.  Large lattices are bound by the
+// factors' bytes (27 of the 36 columns per slice that two full forward and backward sweeps read),
+// small ones, with fewer wavefronts than SIMDs, by the chain.  (M^ee)^-1 in FP32 at 12^3x64 163 ->
+// 82 us, at 16^3x128 510 -> 215 us, at 24^3x128 849 -> 639 us (4.5 TB/s), against four launches that
+// loaded each step's factors when they needed them.  4 and 8 steps ahead: 6 and 12 are no faster,
+// 8 and 16 take 92 us at 12^3x64.
+template <typename T>
+__global__ __launch_bounds__(64) void k_s3_solve(Sweep<T> a, int64_t V2, Geom g) {
   using R = typename Prec<T>::R;
-  __shared__ cx<R> xb[4][12];
+  constexpr int kDeep12 = sizeof(T) == 16 ? 2 : 4, kDeep = sizeof(T) == 16 ? 4 : 8;  // steps ahead of sweep 1 (12 columns) and of the others (6)
+  __shared__ cx<R> zb[48];
   const SweepLane ln = sweep_lane();
-  const T* wp = ln.active ? (ln.r < 6 ? a.in_up[ln.k] : a.in_lo[ln.k]) : nullptr;
-  T* xp = ln.active && a.out_up[ln.k] ? (ln.r < 6 ? a.out_up[ln.k] : a.out_lo[ln.k]) : nullptr;
-  const T* bp =
-      ln.active && a.base_up[ln.k] ? (ln.r < 6 ? a.base_up[ln.k] : a.base_lo[ln.k]) : nullptr;
-  T* qout = a.qout[ln.k];
-  const T* sbase = a.sinv[ln.k] + (int64_t)ln.tile * g.Lt * 576 + ln.lane;
-#pragma unroll 1
-  for (int t = g.Lt - 1; t >= 0; --t) {
-    const int64_t i = p3_idx(g, t, ln.s);
-    cx<R> x = czero<R>();
-    if (ln.active) {
-      x = ld<R, T>(wp + row_off<T>(ln.r, V2, i));
-      if (t < g.Lt - 1) {
-        const T* sc = sbase + (int64_t)t * 576;
+  const int Lt = g.Lt, lane = ln.active ? ln.lane : 0;
+  const bool up = ln.r < 6;
+  // inactive lanes load what lane 0 does and store nothing
+  const int r = ln.active ? ln.r : 0;
+  const int s = ln.active ? ln.s : ln.tile * 4;
+  const int64_t i0 = p3_idx(g, 0, s);
+  const int64_t e0 = row_off<T>(r, V2, i0);
+  const int64_t es = row_off<T>(r, V2, i0 + kTile) - e0;  // elements from one slice to the next
+  const T* ep = (r < 6 ? a.in_up[ln.k] : a.in_lo[ln.k]) + e0;
+  T* wp = (r < 6 ? a.w_up[ln.k] : a.w_lo[ln.k]) + e0;
+  const T* S = a.sinv[ln.k] + (int64_t)ln.tile * Lt * 576 + lane;
+  auto at_t = [&](int t) { return t < 0 ? 0 : (t < Lt ? t : Lt - 1); };  // loads ahead stay in the line
+  // sum of factor columns C0 .. C0+N-1 (in f) times the published values
+  auto mul = [&](const T* f, int c0, auto n) {
+    constexpr int N = decltype(n)::value;
+    cx<R> p[2] = {czero<R>(), czero<R>()};  // two chains
 #pragma unroll
-        for (int c = 6; c < 12; ++c) x += cmul(ld<R, T>(sc + c * 48), xb[ln.l][c]);
-      }
+    for (int c = 0; c < N; ++c) p[c & 1] += cmul(cx<R>{R(f[c].x), R(f[c].y)}, zb[(c0 + c) * 4 + ln.l]);
+    return p[0] + p[1];
+  };
+  using N6 = std::integral_constant<int, 6>;
+  using N12 = std::integral_constant<int, 12>;
+
+  // 1
+  cx<R> prev = czero<R>();
+  {
+    T f[kDeep12][12], e[kDeep12];
+#pragma unroll
+    for (int d = 0; d < kDeep12; ++d) {
+#pragma unroll
+      for (int c = 0; c < 12; ++c) f[d][c] = S[(int64_t)at_t(d) * 576 + c * 48];
+      e[d] = ep[at_t(d) * es];
     }
-    __syncthreads();  // every lane has read x(t+1)
-    if (ln.active) {
-      if (ln.r >= 6) xb[ln.l][ln.r] = x;
-      if (xp) {
-        const int64_t o = row_off<T>(ln.r, V2, i);
-        st(xp + o, bp ? ld<R, T>(bp + o) - x : x);
+#pragma unroll 1
+    for (int t0 = 0; t0 < Lt; t0 += kDeep12)
+#pragma unroll
+      for (int d = 0; d < kDeep12; ++d) {
+        const int t = t0 + d;
+        if (t >= Lt) break;
+        cx<R> z = cx<R>{R(e[d].x), R(e[d].y)};
+        if (up) z += prev;
+        wave_sync();
+        if (ln.active) zb[ln.lane] = z;
+        wave_sync();
+        prev = mul(f[d], 0, N12{});
+        if (ln.active) st(wp + t * es, prev);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) f[d][c] = S[(int64_t)at_t(t + kDeep12) * 576 + c * 48];
+        e[d] = ep[at_t(t + kDeep12) * es];
       }
-      if (qout && ((t == g.Lt - 1 && ln.r < 6) || (t == 0 && ln.r >= 6)))
-        st(qout + (int64_t)ln.s * 12 + ln.r, x);
+  }
+  // 2: y on the lower rows (lanes of upper rows follow along); y(Lt-1) = w_lo(Lt-1)
+  const cx<R> wlast = prev;
+  {
+    T f[kDeep][6], e[kDeep];
+#pragma unroll
+    for (int d = 0; d < kDeep; ++d) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) f[d][c] = up ? T{} : S[(int64_t)at_t(Lt - 2 - d) * 576 + (6 + c) * 48];
+      e[d] = up ? T{} : wp[at_t(Lt - 2 - d) * es];
     }
-    __syncthreads();
+#pragma unroll 1
+    for (int t0 = Lt - 2; t0 >= 0; t0 -= kDeep)
+#pragma unroll
+      for (int d = 0; d < kDeep; ++d) {
+        const int t = t0 - d;
+        if (t < 0) break;
+        wave_sync();
+        if (ln.active) zb[ln.lane] = prev;
+        wave_sync();
+        prev = cx<R>{R(e[d].x), R(e[d].y)} + mul(f[d], 6, N6{});
+#pragma unroll
+        for (int c = 0; c < 6; ++c) f[d][c] = up ? T{} : S[(int64_t)at_t(t - kDeep) * 576 + (6 + c) * 48];
+        e[d] = up ? T{} : wp[at_t(t - kDeep) * es];
+      }
+  }
+  // beta = K q and this lane's corner term: rows 0-5 at t = 0, rows 6-11 at t = Lt-1
+  wave_sync();
+  if (ln.active) zb[ln.lane] = up ? wlast : prev;
+  wave_sync();
+  cx<R> beta = czero<R>();
+  {
+    const T* kr = a.kmat[ln.k] + (int64_t)s * 144 + r * 12;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) beta += cmul(ld<R, T>(kr + c), zb[c * 4 + ln.l]);
+  }
+  wave_sync();
+  if (ln.active) zb[ln.lane] = beta;
+  wave_sync();
+  cx<R> corr = czero<R>();
+  if (ln.active) corr = corner_term<R>(a.link_t[ln.k], ln, V2, g, [&](int k) { return zb[k * 4 + ln.l]; });
+  // 3
+  {
+    T f[kDeep][6], e[kDeep];
+#pragma unroll
+    for (int d = 0; d < kDeep; ++d) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) f[d][c] = S[(int64_t)at_t(d) * 576 + c * 48];
+      e[d] = wp[at_t(d) * es];
+    }
+    prev = corr;  // what the upper rows publish at t = 0
+#pragma unroll 1
+    for (int t0 = 0; t0 < Lt; t0 += kDeep)
+#pragma unroll
+      for (int d = 0; d < kDeep; ++d) {
+        const int t = t0 + d;
+        if (t >= Lt) break;
+        wave_sync();
+        // the lower rows of the corner term enter at t = Lt-1, after the loop
+        if (ln.active) zb[ln.lane] = up ? prev : corr;
+        wave_sync();
+        prev = mul(f[d], 0, N6{});
+        const cx<R> w = cx<R>{R(e[d].x), R(e[d].y)} + prev;
+        if (ln.active && t < Lt - 1) st(wp + t * es, w);
+        if (t == Lt - 1) prev = w;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) f[d][c] = S[(int64_t)at_t(t + kDeep) * 576 + c * 48];
+        e[d] = wp[at_t(t + kDeep) * es];
+      }
+    T fl[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) fl[c] = S[(int64_t)(Lt - 1) * 576 + (6 + c) * 48];
+    prev += mul(fl, 6, N6{});  // x(Lt-1) = w(Lt-1)
+  }
+  // 4
+  {
+    T* xp = (r < 6 ? a.out_up[ln.k] : a.out_lo[ln.k]) + e0;
+    const T* bp = a.base_up[ln.k] ? (r < 6 ? a.base_up[ln.k] : a.base_lo[ln.k]) + e0 : nullptr;
+    auto put = [&](int t, cx<R> x, T b) {
+      if (ln.active) st(xp + t * es, bp ? cx<R>{R(b.x), R(b.y)} - x : x);
+    };
+    put(Lt - 1, prev, bp ? bp[(Lt - 1) * es] : T{});
+    T f[kDeep][6], e[kDeep], bb[kDeep];
+#pragma unroll
+    for (int d = 0; d < kDeep; ++d) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) f[d][c] = S[(int64_t)at_t(Lt - 2 - d) * 576 + (6 + c) * 48];
+      e[d] = wp[at_t(Lt - 2 - d) * es];
+      bb[d] = bp ? bp[at_t(Lt - 2 - d) * es] : T{};
+    }
+#pragma unroll 1
+    for (int t0 = Lt - 2; t0 >= 0; t0 -= kDeep)
+#pragma unroll
+      for (int d = 0; d < kDeep; ++d) {
+        const int t = t0 - d;
+        if (t < 0) break;
+        wave_sync();
+        if (ln.active) zb[ln.lane] = prev;
+        wave_sync();
+        prev = cx<R>{R(e[d].x), R(e[d].y)} + mul(f[d], 6, N6{});
+        put(t, prev, bb[d]);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) f[d][c] = S[(int64_t)at_t(t - kDeep) * 576 + (6 + c) * 48];
+        e[d] = wp[at_t(t - kDeep) * es];
+        bb[d] = bp ? bp[at_t(t - kDeep) * es] : T{};
+      }
   }
 }
 
@@ -370,22 +528,8 @@ void schur3d_setup(tp_op op, int par) {
     LAUNCH_CHECK();
     SpinorF<double2> wf = w.par<double2>(par);
     for (int j = 0; j < 12; ++j) {
-      Sweep<double2> f;
-      f.out_up[0] = wf.p[0];
-      f.out_lo[0] = wf.p[1];
-      f.sinv[0] = sinv;
-      f.link_t[0] = op->g->u3_d + (int64_t)(3 * 2 + par) * 9 * L.V2;
-      f.unit = j;
-      hipLaunchKernelGGL(k_s3_forward<double2>, dim3(nlines / 4, 1), dim3(64), 0, ctx->stream, f,
-                         L.V2, L.g);
-      LAUNCH_CHECK();
-      Sweep<double2> b;
-      b.in_up[0] = wf.p[0];
-      b.in_lo[0] = wf.p[1];
-      b.sinv[0] = sinv;
-      b.qout[0] = qbuf + (int64_t)j * nlines * 12;
-      hipLaunchKernelGGL(k_s3_backward<double2>, dim3(nlines / 4, 1), dim3(64), 0, ctx->stream, b,
-                         L.V2, L.g);
+      hipLaunchKernelGGL(k_s3_unit, dim3(nlines / 4, 1), dim3(64), 0, ctx->stream, wf.p[0], wf.p[1], sinv,
+                         op->g->u3_d + (int64_t)(3 * 2 + par) * 9 * L.V2, qbuf + (int64_t)j * nlines * 12, j, L.V2, L.g);
       LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(k_s3_capacitance, dim3(nblk), dim3(kFacThreads),
@@ -406,9 +550,9 @@ void schur3d_setup(tp_op op, int par) {
   }
   field_free(ctx, w);
   dev_free(ctx, bad);
+  dev_free(ctx, qbuf);
   op->s3_inv[par] = sinv;
   op->s3_k[par] = kmat;
-  op->s3_q[par] = qbuf;  // the first 12 complex per line serve the applies
 }
 
 namespace {
@@ -421,10 +565,8 @@ void schur3d_setup_f32(tp_op op, int par) {
   const int64_t ni = L.V2 * 144, nk = int64_t(L.Vs2) * 144;
   float2* fi = static_cast<float2*>(dev_alloc(ctx, size_t(ni) * sizeof(float2)));
   float2* fk = nullptr;
-  float2* fq = nullptr;
   try {
     fk = static_cast<float2*>(dev_alloc(ctx, size_t(nk) * sizeof(float2)));
-    fq = static_cast<float2*>(dev_alloc(ctx, size_t(L.Vs2) * 12 * sizeof(float2)));
     hipLaunchKernelGGL(k_s3_round, dim3(unsigned((ni + 255) / 256)), dim3(256), 0, ctx->stream,
                        op->s3_inv[par], fi, ni);
     LAUNCH_CHECK();
@@ -433,14 +575,12 @@ void schur3d_setup_f32(tp_op op, int par) {
     LAUNCH_CHECK();
     HIP_CHECK(hipStreamSynchronize(ctx->stream));
   } catch (...) {
-    dev_free(ctx, fq);
     dev_free(ctx, fk);
     dev_free(ctx, fi);
     throw;
   }
   op->s3_inv_f[par] = fi;
   op->s3_k_f[par] = fk;
-  op->s3_q_f[par] = fq;
 }
 }  // namespace
 
@@ -453,59 +593,42 @@ void schur3d_free(tp_op op) {
   for (int p = 0; p < 2; ++p) {
     dev_free(ctx, op->s3_inv[p]);
     dev_free(ctx, op->s3_k[p]);
-    dev_free(ctx, op->s3_q[p]);
     dev_free(ctx, op->s3_inv_f[p]);
     dev_free(ctx, op->s3_k_f[p]);
-    dev_free(ctx, op->s3_q_f[p]);
-    op->s3_inv[p] = op->s3_k[p] = op->s3_q[p] = nullptr;
-    op->s3_inv_f[p] = op->s3_k_f[p] = op->s3_q_f[p] = nullptr;
+    op->s3_inv[p] = op->s3_k[p] = nullptr;
+    op->s3_inv_f[p] = op->s3_k_f[p] = nullptr;
   }
 }
 
 namespace {
-// Two solves of T0 per parity (Sherman-Morrison-Woodbury): the first only yields the
-// boundary values q = W^dag T0^-1 src, the second adds the corner term K q.  Both parities
-// of a call run in the same launches (blockIdx.y).
 template <typename T>
 void tinv_impl(tp_op op, int par0, int npar, const Field& src, Field& dst, Field& w,
-               const Field* base, T* const* sinv, T* const* kmat, T* const* q) {
+               const Field* base, T* const* sinv, T* const* kmat) {
   tp_ctx ctx = op->g->ctx;
   const Lattice& L = ctx->lat;
-  const dim3 grid(L.Vs2 / 4, npar);
   for (int r = 0; r < src.nr; ++r) {
-    Sweep<T> f1, b1, f2, b2;
+    Sweep<T> a;
     for (int k = 0; k < npar; ++k) {
       const int p = par0 + k;
       SpinorF<T> sf = src.view(r).template par<T>(p);
       SpinorF<T> df = dst.view(r).template par<T>(p);
       SpinorF<T> wf = w.view(r).template par<T>(p);
-      const double2* link_t = op->g->u3_d + (int64_t)(3 * 2 + p) * 9 * L.V2;
-      f1.in_up[k] = f2.in_up[k] = sf.p[0];
-      f1.in_lo[k] = f2.in_lo[k] = sf.p[1];
-      f1.out_up[k] = f2.out_up[k] = wf.p[0];
-      f1.out_lo[k] = f2.out_lo[k] = wf.p[1];
-      f1.sinv[k] = f2.sinv[k] = b1.sinv[k] = b2.sinv[k] = sinv[p];
-      f1.link_t[k] = f2.link_t[k] = link_t;
-      f2.kmat[k] = kmat[p];
-      f2.q[k] = q[p];
-      b1.in_up[k] = b2.in_up[k] = wf.p[0];
-      b1.in_lo[k] = b2.in_lo[k] = wf.p[1];
-      b1.qout[k] = q[p];
-      b2.out_up[k] = df.p[0];
-      b2.out_lo[k] = df.p[1];
+      a.in_up[k] = sf.p[0];
+      a.in_lo[k] = sf.p[1];
+      a.w_up[k] = wf.p[0];
+      a.w_lo[k] = wf.p[1];
+      a.out_up[k] = df.p[0];
+      a.out_lo[k] = df.p[1];
+      a.sinv[k] = sinv[p];
+      a.kmat[k] = kmat[p];
+      a.link_t[k] = op->g->u3_d + (int64_t)(3 * 2 + p) * 9 * L.V2;
       if (base) {
         SpinorF<T> bf = base->view(r).template par<T>(p);
-        b2.base_up[k] = bf.p[0];
-        b2.base_lo[k] = bf.p[1];
+        a.base_up[k] = bf.p[0];
+        a.base_lo[k] = bf.p[1];
       }
     }
-    hipLaunchKernelGGL(k_s3_forward<T>, grid, dim3(64), 0, ctx->stream, f1, L.V2, L.g);
-    LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_s3_backward<T>, grid, dim3(64), 0, ctx->stream, b1, L.V2, L.g);
-    LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_s3_forward<T>, grid, dim3(64), 0, ctx->stream, f2, L.V2, L.g);
-    LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_s3_backward<T>, grid, dim3(64), 0, ctx->stream, b2, L.V2, L.g);
+    hipLaunchKernelGGL(k_s3_solve<T>, dim3(L.Vs2 / 4, npar), dim3(64), 0, ctx->stream, a, L.V2, L.g);
     LAUNCH_CHECK();
   }
 }
@@ -525,12 +648,13 @@ void launch_tinv(tp_op op, int par0, int npar, const Field& src, Field& dst, Fie
     else schur3d_setup_f32(op, p);
   }
   const double fb = src.prec == TP_F64 ? 16.0 : 8.0;
-  const double spin = (7 + (base ? 1 : 0)) * spinor_bytes(src.prec);
-  ProfScope ps(ctx, KID_SCHUR3D_MEE, double(L.V2) * (2 * (144 + 72) * fb + spin) * src.nr * npar);
+  // factors: 144 + 36 + 72 + 72; eta and w, half of w, w twice, w and x (and the base)
+  const double spin = (6.5 + (base ? 1 : 0)) * spinor_bytes(src.prec);
+  ProfScope ps(ctx, KID_SCHUR3D_MEE, double(L.V2) * (324 * fb + spin) * src.nr * npar);
   if (src.prec == TP_F64)
-    tinv_impl<double2>(op, par0, npar, src, dst, w, base, op->s3_inv, op->s3_k, op->s3_q);
+    tinv_impl<double2>(op, par0, npar, src, dst, w, base, op->s3_inv, op->s3_k);
   else
-    tinv_impl<float2>(op, par0, npar, src, dst, w, base, op->s3_inv_f, op->s3_k_f, op->s3_q_f);
+    tinv_impl<float2>(op, par0, npar, src, dst, w, base, op->s3_inv_f, op->s3_k_f);
 }
 
 // dst_e = (M^ee)^-1 src_e for each right-hand side of the batch, in the fields' precision

@@ -189,10 +189,8 @@ struct tp_op_s {
   // serves the 3D-Schur scheme, both the whole-lattice full-SW scheme):
   double2* s3_inv[2] = {};  // block-LU S(t)^-1 [tile][t][12 col][12 row][4 line]
   double2* s3_k[2] = {};    // Woodbury capacitance K per line [Vs2][12][12]
-  double2* s3_q[2] = {};    // boundary values W^dag T0^-1 eta [Vs2][12] (set-up: [12][Vs2][12])
   float2* s3_inv_f[2] = {};  // the factors rounded to FP32 for the FP32 operator
   float2* s3_k_f[2] = {};
-  float2* s3_q_f[2] = {};
   Workspace* ws = nullptr;
   int batch_nr = 1;  // right-hand sides of the batched apply in progress (workspace size)
   // No-allocation mode (tp_apply_prec_noalloc): while arena is set, workspace fields are
