@@ -291,14 +291,16 @@ int noalloc_fields(int scheme) {
 // device-side scalars.
 void ctx_buffers_alloc(tp_ctx c) {
   c->red_partial = static_cast<double*>(dev_alloc(c, sizeof(double) * 8 * kRedBlocks));
-  c->red_result = static_cast<double*>(dev_alloc(c, sizeof(double) * (8 * kMaxRhs + BS_COUNT)));
+  c->red_result = static_cast<double*>(dev_alloc(c, sizeof(double) * (9 * kMaxRhs + BS_COUNT)));
   c->bicg = c->red_result + 8 * kMaxRhs;
-  HIP_CHECK(hipMemsetAsync(c->bicg, 0, sizeof(double) * BS_COUNT, c->stream));
+  c->red_ticket = reinterpret_cast<unsigned*>(c->bicg + BS_COUNT);
+  HIP_CHECK(hipMemsetAsync(c->bicg, 0, sizeof(double) * (kMaxRhs + BS_COUNT), c->stream));
 }
 void ctx_buffers_free(tp_ctx c) {
   dev_free(c, c->red_partial);
   dev_free(c, c->red_result);
   c->red_partial = c->red_result = c->bicg = nullptr;
+  c->red_ticket = nullptr;
 }
 
 // Canonical-in / canonical-out wrapper for the internal applies.

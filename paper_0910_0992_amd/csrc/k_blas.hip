@@ -14,6 +14,130 @@ constexpr int kBlock = 256;
 constexpr int kBlasBlocks = 1024;
 static_assert(kBlasBlocks <= kRedBlocks, "partials buffer too small");
 
+static_assert(BS_COUNT <= 8 * kMaxRhs, "pinned staging buffer too small for the solver scalars");
+
+// BiCGStab's scalar steps on the device (single right-hand side), from the reduced values v
+// of the op just finished; the same formulas as the host-side solver.
+TP_DEV void bicg_post(int post, const double* v, double* st) {
+  if (post == BP_RHO) {
+    st[BS_RHO] = v[0];
+    st[BS_RHO + 1] = v[1];
+  } else if (post == BP_ALPHA) {  // v = <rhat, v>
+    const double den = v[0] * v[0] + v[1] * v[1];
+    const double rr = st[BS_RHO], ri = st[BS_RHO + 1];
+    const double ar = (rr * v[0] + ri * v[1]) / den, ai = (ri * v[0] - rr * v[1]) / den;
+    st[BS_ALPHA] = ar;
+    st[BS_ALPHA + 1] = ai;
+    st[BS_AXPY] = -ar;
+    st[BS_AXPY + 1] = -ai;
+    for (int q = 2; q < 6; ++q) st[BS_AXPY + q] = 0.0;
+  } else if (post == BP_S2) {
+    st[BS_S2] = v[0];
+  } else if (post == BP_OMEGA) {  // v = <t, s>, |t|^2, <rhat, s>, <rhat, t>
+    const double om_r = v[0] / v[2], om_i = v[1] / v[2];
+    const double rn_r = v[3] - (om_r * v[5] - om_i * v[6]);
+    const double rn_i = v[4] - (om_r * v[6] + om_i * v[5]);
+    const double rho_r = st[BS_RHO], rho_i = st[BS_RHO + 1];
+    const double al_r = st[BS_ALPHA], al_i = st[BS_ALPHA + 1];
+    const double rr = rho_r * rho_r + rho_i * rho_i, oo = om_r * om_r + om_i * om_i;
+    const double q_r = (rn_r * rho_r + rn_i * rho_i) / rr, q_i = (rn_i * rho_r - rn_r * rho_i) / rr;
+    const double w_r = (al_r * om_r + al_i * om_i) / oo, w_i = (al_i * om_r - al_r * om_i) / oo;
+    const double be_r = q_r * w_r - q_i * w_i, be_i = q_r * w_i + q_i * w_r;
+    st[BS_BREAK] = (v[2] == 0.0 || !isfinite(oo) || oo == 0.0 || rr == 0.0) ? 1.0 : 0.0;
+    st[BS_OMEGA] = om_r;
+    st[BS_OMEGA + 1] = om_i;
+    st[BS_BETA] = be_r;
+    st[BS_BETA + 1] = be_i;
+    st[BS_FUSED] = al_r;
+    st[BS_FUSED + 1] = al_i;
+    st[BS_FUSED + 2] = om_r;
+    st[BS_FUSED + 3] = om_i;
+    st[BS_FUSED + 4] = be_r;
+    st[BS_FUSED + 5] = be_i;
+    st[BS_RHO] = rn_r;
+    st[BS_RHO + 1] = rn_i;
+  } else if (post == BP_R2) {
+    st[BS_R2] = v[0];
+  }
+}
+
+// Sums nblocks rows of partials in a fixed order (the calling workgroup: kBlock threads), writes
+// the sums to result and runs the solver's scalar step on them.  SHARED: the partials come from
+// workgroups of the same launch (on other XCDs), by device-scope accesses.  The NRED sums share
+// their loads' latency and the barriers of the tree.
+template <int NRED, bool SHARED>
+TP_DEV void sum_partials(const double* partial, int nblocks, double* result, int post, double* st) {
+  __shared__ double sh[NRED][kBlock];
+  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int b = threadIdx.x; b < nblocks; b += kBlock) {
+#pragma unroll
+    for (int k = 0; k < NRED; ++k) {
+      const double* p = partial + (int64_t)b * 8 + k;
+      v[k] += SHARED ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NRED; ++k) sh[k][threadIdx.x] = v[k];
+  __syncthreads();
+  for (int w = kBlock / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) {
+#pragma unroll
+      for (int k = 0; k < NRED; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + w];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < NRED; ++k) result[k] = v[k] = sh[k][0];
+    if (post != BP_NONE) bicg_post(post, v, st);
+  }
+}
+
+// The reduction's end inside the kernel that made the partials: the last workgroup of a right-hand
+// side to take a ticket sums them (in k_finish's order).  A separate launch costs a small lattice
+// more than the sums; tickets return to zero for the next reduction on the stream.
+struct Finish {
+  unsigned* ticket;  // one per right-hand side, zero between reductions; null: k_finish follows
+  double* result;
+  double* st;
+  int post;
+};
+
+template <int nred>
+TP_DEV void block_reduce(double (&acc)[8], double* partial, uint32_t blk, uint32_t nblk, uint32_t rhs,
+                         const Finish& fin) {
+  __shared__ double sh[kBlock / 64][8];
+  __shared__ int last;
+  for (int k = 0; k < nred; ++k) {
+    double v = acc[k];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < (unsigned)nred) {
+    double s = 0;
+    for (int w = 0; w < kBlock / 64; ++w) s += sh[w][threadIdx.x];
+    if (fin.ticket)
+      __hip_atomic_store(partial + (int64_t)blk * 8 + threadIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      partial[(int64_t)blk * 8 + threadIdx.x] = s;
+  }
+  if (!fin.ticket) return;
+  // The partials were stored by lanes of this thread's own wavefront (nred < 64), at device scope
+  // (through the XCD's L2): once its counter of outstanding stores is zero they are where every XCD
+  // reads them, and only then the ticket is taken.  A release at device scope would write back the
+  // whole L2 first (35 us more with 1024 workgroups).
+  if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const unsigned t = __hip_atomic_fetch_add(fin.ticket + rhs, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = t == nblk - 1;
+    if (last) __hip_atomic_store(fin.ticket + rhs, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!last) return;
+  sum_partials<nred, true>(partial, int(nblk), fin.result + (int64_t)rhs * 8, rhs == 0 ? fin.post : int(BP_NONE), fin.st);
+}
+
 template <typename S>
 struct BlasK {
   SpinorF<S> f[6][2];
@@ -24,24 +148,8 @@ struct BlasK {
   double coef[kMaxRhs][8];     // nr > 1: per right-hand side a, b, c (complex) and a skip flag
   double* partial;             // [nr][blocks per right-hand side][8]
   const double* dcoef;         // single right-hand side: a, b, c read from device memory
+  Finish fin;
 };
-static_assert(BS_COUNT <= 8 * kMaxRhs, "pinned staging buffer too small for the solver scalars");
-
-TP_DEV void block_reduce(double (&acc)[8], int nred, double* partial, uint32_t blk) {
-  __shared__ double sh[kBlock / 64][8];
-  for (int k = 0; k < nred; ++k) {
-    double v = acc[k];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < (unsigned)nred) {
-    double s = 0;
-    for (int w = 0; w < kBlock / 64; ++w) s += sh[w][threadIdx.x];
-    partial[(int64_t)blk * 8 + threadIdx.x] = s;
-  }
-}
-
 template <typename R> TP_DEV cx<R> cc(const double* z) { return cx<R>{R(z[0]), R(z[1])}; }
 
 // The reductions that write no field (norms and inner products) read each field once, in vectors
@@ -169,7 +277,7 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
       : (OP == B_DOT) ? 2
       : (OP == B_DOT_NORM) ? 3
       : (OP == B_DOT4_TS) ? 7 : 0;
-  if constexpr (nred > 0) block_reduce(acc, nred, k.partial + (int64_t)rhs * nblk * 8, blk);
+  if constexpr (nred > 0) block_reduce<nred>(acc, k.partial + (int64_t)rhs * nblk * 8, blk, nblk, rhs, k.fin);
 }
 
 // y (precision SY) = x (precision SX) when MODE = 0, y += x when MODE = 1, y = z + x (z in
@@ -198,72 +306,26 @@ __global__ void __launch_bounds__(kBlock) k_convert(SpinorF<SX> x0, SpinorF<SX> 
   }
 }
 
-// BiCGStab's scalar steps on the device (single right-hand side), from the reduced values v
-// of the op just finished; the same formulas as the host-side solver.
-TP_DEV void bicg_post(int post, const double* v, double* st) {
-  if (post == BP_RHO) {
-    st[BS_RHO] = v[0];
-    st[BS_RHO + 1] = v[1];
-  } else if (post == BP_ALPHA) {  // v = <rhat, v>
-    const double den = v[0] * v[0] + v[1] * v[1];
-    const double rr = st[BS_RHO], ri = st[BS_RHO + 1];
-    const double ar = (rr * v[0] + ri * v[1]) / den, ai = (ri * v[0] - rr * v[1]) / den;
-    st[BS_ALPHA] = ar;
-    st[BS_ALPHA + 1] = ai;
-    st[BS_AXPY] = -ar;
-    st[BS_AXPY + 1] = -ai;
-    for (int q = 2; q < 6; ++q) st[BS_AXPY + q] = 0.0;
-  } else if (post == BP_S2) {
-    st[BS_S2] = v[0];
-  } else if (post == BP_OMEGA) {  // v = <t, s>, |t|^2, <rhat, s>, <rhat, t>
-    const double om_r = v[0] / v[2], om_i = v[1] / v[2];
-    const double rn_r = v[3] - (om_r * v[5] - om_i * v[6]);
-    const double rn_i = v[4] - (om_r * v[6] + om_i * v[5]);
-    const double rho_r = st[BS_RHO], rho_i = st[BS_RHO + 1];
-    const double al_r = st[BS_ALPHA], al_i = st[BS_ALPHA + 1];
-    const double rr = rho_r * rho_r + rho_i * rho_i, oo = om_r * om_r + om_i * om_i;
-    const double q_r = (rn_r * rho_r + rn_i * rho_i) / rr, q_i = (rn_i * rho_r - rn_r * rho_i) / rr;
-    const double w_r = (al_r * om_r + al_i * om_i) / oo, w_i = (al_i * om_r - al_r * om_i) / oo;
-    const double be_r = q_r * w_r - q_i * w_i, be_i = q_r * w_i + q_i * w_r;
-    st[BS_BREAK] = (v[2] == 0.0 || !isfinite(oo) || oo == 0.0 || rr == 0.0) ? 1.0 : 0.0;
-    st[BS_OMEGA] = om_r;
-    st[BS_OMEGA + 1] = om_i;
-    st[BS_BETA] = be_r;
-    st[BS_BETA + 1] = be_i;
-    st[BS_FUSED] = al_r;
-    st[BS_FUSED + 1] = al_i;
-    st[BS_FUSED + 2] = om_r;
-    st[BS_FUSED + 3] = om_i;
-    st[BS_FUSED + 4] = be_r;
-    st[BS_FUSED + 5] = be_i;
-    st[BS_RHO] = rn_r;
-    st[BS_RHO + 1] = rn_i;
-  } else if (post == BP_R2) {
-    st[BS_R2] = v[0];
-  }
-}
-
-// Block r sums the `nblocks` partials of right-hand side r into result[r][0..nred); with
+// Block r sums the `nblocks` partials of right-hand side r into result[r][0..NRED); with
 // `post`, block 0 then updates the solver scalars st.
-__global__ void k_finish(const double* partial, int nblocks, int nred, double* result, int post,
-                         double* st) {
-  __shared__ double sh[kBlock];
-  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  partial += (int64_t)blockIdx.x * nblocks * 8;
-  result += (int64_t)blockIdx.x * 8;
-  for (int k = 0; k < nred; ++k) {
-    double s = 0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) s += partial[(int64_t)b * 8 + k];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) result[k] = v[k] = sh[0];
-    __syncthreads();
+template <int NRED>
+__global__ void __launch_bounds__(kBlock) k_finish(const double* partial, int nblocks, double* result, int post,
+                                                   double* st) {
+  sum_partials<NRED, false>(partial + (int64_t)blockIdx.x * nblocks * 8, nblocks, result + (int64_t)blockIdx.x * 8,
+                            blockIdx.x == 0 ? post : int(BP_NONE), st);
+}
+void finish_go(tp_ctx ctx, int nr, int nb, int nred, int post) {
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(nr), dim3(kBlock), 0, ctx->stream, ctx->red_partial, nb, ctx->red_result, post,
+                       ctx->bicg);
+  };
+  switch (nred) {
+    case 1: go(k_finish<1>); break;
+    case 2: go(k_finish<2>); break;
+    case 3: go(k_finish<3>); break;
+    default: go(k_finish<7>); break;
   }
-  if (post != BP_NONE && blockIdx.x == 0 && threadIdx.x == 0) bicg_post(post, v, st);
+  LAUNCH_CHECK();
 }
 
 template <typename S>
@@ -283,8 +345,16 @@ struct BlasCall {
   const BlasArgs* per;
   const bool* skip;
   const double* dcoef;
+  int post;
 };
 
+// Largest grid whose last workgroup ends the reduction.  Kernel and k_finish against the kernel
+// alone (a launch between them costs about 2.5 us more): 256 workgroups (8^3x64, F16N) 7.0 + 4.0
+// against 8.8 us for <x, y>, 8.9 + 5.0 against 13.5 us for the four dots; 1024 (12^3x64, F64) 8.9 +
+// 4.6 against 17.6 and 17.3 + 4.8 against 27.3 us, the tickets being taken one after another.
+constexpr int64_t kTicketBlocks = 256;
+
+// Returns the workgroups per right-hand side, or 0 when the kernel has ended its reduction itself.
 template <typename S, int OP>
 int blas_go(tp_ctx ctx, int par0, int npar, const Field* const* fs, const BlasCall& c) {
   BlasK<S> a;
@@ -314,9 +384,11 @@ int blas_go(tp_ctx ctx, int par0, int npar, const Field* const* fs, const BlasCa
   // 5.0 TB/s at 4), FP16 ones with 4 (4.5 against 4.4 at 2 or 16)
   const int blocks = std::is_same<S, float2>::value ? kBlasBlocks / 2 : kBlasBlocks;
   nb = std::min<int64_t>(nb, std::max(1, blocks / c.nr));
+  const bool own = nb * c.nr <= kTicketBlocks;
+  a.fin = Finish{own ? ctx->red_ticket : nullptr, ctx->red_result, ctx->bicg, c.post};
   hipLaunchKernelGGL((k_blas<S, OP>), dim3((unsigned)(nb * c.nr)), dim3(kBlock), 0, ctx->stream, a);
   LAUNCH_CHECK();
-  return int(nb);
+  return own ? 0 : int(nb);
 }
 
 template <int OP>
@@ -406,7 +478,7 @@ void blas_impl(tp_ctx ctx, BlasOp op, int par0, int npar, std::initializer_list<
   }
   if (nr < 1 || nr > kMaxRhs) TP_THROW(TP_EINVAL, "blas: batch size");
   if (dev && nr != 1) TP_THROW(TP_EINVAL, "blas: device-side coefficients take single fields");
-  const BlasCall call{k, nr, per, skip, dcoef};
+  const BlasCall call{k, nr, per, skip, dcoef, post};
   const Field* x = fs[0];
   const Field* y = fs[1];
   int prec = x ? x->prec : y->prec;
@@ -463,11 +535,9 @@ void blas_impl(tp_ctx ctx, BlasOp op, int par0, int npar, std::initializer_list<
     }
   }
   if (nred > 0) {
-    {
+    if (nb > 0) {
       ProfScope ps(ctx, KID_REDUCE, double(nb) * nr * 8 * 8);
-      hipLaunchKernelGGL(k_finish, dim3(nr), dim3(kBlock), 0, ctx->stream, ctx->red_partial, nb, nred,
-                         ctx->red_result, post, ctx->bicg);
-      LAUNCH_CHECK();
+      finish_go(ctx, nr, nb, nred, post);
     }
     if (dev) return;
     HIP_CHECK(hipMemcpyAsync(ctx->red_host, ctx->red_result, sizeof(double) * 8 * nr,
@@ -481,9 +551,7 @@ void blas_impl(tp_ctx ctx, BlasOp op, int par0, int npar, std::initializer_list<
 
 // Sum of the first `nblocks` partials written by a norm-producing site kernel.
 double finish_norm(tp_ctx ctx, int nblocks) {
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(kBlock), 0, ctx->stream, ctx->red_partial, nblocks, 1,
-                     ctx->red_result, int(BP_NONE), ctx->bicg);
-  LAUNCH_CHECK();
+  finish_go(ctx, 1, nblocks, 1, BP_NONE);
   HIP_CHECK(hipMemcpyAsync(ctx->red_host, ctx->red_result, sizeof(double), hipMemcpyDeviceToHost,
                            ctx->stream));
   HIP_CHECK(hipStreamSynchronize(ctx->stream));

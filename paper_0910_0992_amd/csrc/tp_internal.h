@@ -119,6 +119,7 @@ struct tp_ctx_s {
   double* red_partial = nullptr;  // [kRedBlocks][8]
   double* red_result = nullptr;   // [8]
   double* red_host = nullptr;     // pinned [8]
+  unsigned* red_ticket = nullptr; // [kMaxRhs] workgroups done with a reduction (inside red_result's allocation)
   // BiCGStab scalars kept on the device (inside red_result's allocation): see BicgSlot
   double* bicg = nullptr;
   // device memory: registered allocator (null: hipMalloc), live allocations and their sizes

@@ -134,3 +134,23 @@ def test_canonical_applies(dims, clover, cut):
     assert L.tp_apply_M(g._op, 0, C.c_void_p(buf[12:].data_ptr()), C.c_void_p(buf.data_ptr()), 0) == 0
     assert _rel(g.apply_M(t).reshape(-1), buf[12:].cpu().numpy()) < TOL64
     g.close()
+
+
+# reductions end in the kernel's last workgroup up to 256 workgroups (8^3 x 64 in FP64) and in a
+# launch of their own beyond; single and batched, in every precision
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 4, 8), (8, 8, 8, 64), (8, 8, 8, 66)])
+@pytest.mark.parametrize("prec", ["F64", "F32", "F16N"])
+def test_reductions_around_the_ticket_limit(dims, prec):
+    U = synth.make_links(dims, 0.3, 0.1, 1105)
+    from paper_0910_0992_amd import Operator
+    g = Operator(torch.from_numpy(U).cuda(), 0.05, 3.0, 0.5, 1.0, -1)
+    etas = torch.stack([torch.from_numpy(synth.make_source(dims, 2105 + k)).cuda() for k in range(3)])
+    print(f"[case] {dims} {prec}", flush=True)
+    for rep in range(2):  # the tickets are back at zero
+        x, info = g.solve(etas[0], prec=prec, tol=1e-10)
+        assert float((g.apply_M(x) - etas[0]).norm() / etas[0].norm()) < 1.05e-10
+        xs, infos = g.solve_multi(etas, prec=prec, tol=1e-10)
+        for k in range(3):
+            assert float((g.apply_M(xs[k]) - etas[k]).norm() / etas[k].norm()) < 1.05e-10
+            assert infos[k]["true_rel_resid"] <= 1e-10
+    g.close()
