@@ -465,13 +465,18 @@ KrylovResult bicgstab(const KrylovOp& A, const Field& b, Field& y, double eps, i
   blas(ctx, B_COPY, p0, np, {&b, &r});
   blas(ctx, B_COPY, p0, np, {&b, &rh});
   blas(ctx, B_COPY, p0, np, {&b, &p});
-  blas(ctx, B_DOT_NORM, p0, np, {&rh, &r}, BlasArgs{}, red);
-  double bn2 = red[2];
+  blas(ctx, B_NORM2, p0, np, {&r}, BlasArgs{}, red);
+  double bn2 = red[0];
   if (bn2 == 0.0) {
     res.converged = true;
     return res;
   }
-  double rho_r = red[0], rho_i = red[1];
+  // scalars stay on the device and the host reads them once per iteration (see
+  // bicgstab_reliable); an iteration always runs to its end, which keeps the half step when
+  // its second half breaks down
+  double* st = ctx->bicg;
+  double S[BS_COUNT];
+  blas_dev(ctx, B_DOT, p0, np, {&rh, &r}, nullptr, BP_RHO);
   double r2 = bn2;
   const double tgt2 = eps * eps * bn2;
   double best2 = bn2;
@@ -483,57 +488,27 @@ KrylovResult bicgstab(const KrylovOp& A, const Field& b, Field& y, double eps, i
       break;
     }
     A.apply(p, v, false);
-    res.applies++;
-    blas(ctx, B_DOT, p0, np, {&rh, &v}, BlasArgs{}, red);
-    double den = red[0] * red[0] + red[1] * red[1];
-    if (den == 0.0 || !isfinite(den)) { res.breakdown = true; break; }
-    // alpha = rho / <rhat, v>
-    double al_r = (rho_r * red[0] + rho_i * red[1]) / den;
-    double al_i = (rho_i * red[0] - rho_r * red[1]) / den;
-    blas(ctx, B_AXPYZ_NORM, p0, np, {&v, &r, &s}, cplx(-al_r, -al_i), red);
-    double s2 = red[0];
-    res.iters++;
-    if (s2 <= tgt2) {
-      blas(ctx, B_AXPY, p0, np, {&p, &y}, cplx(al_r, al_i));
-      r2 = s2;
-      res.converged = true;
-      break;
-    }
+    blas_dev(ctx, B_DOT, p0, np, {&rh, &v}, nullptr, BP_ALPHA_ROUNDED);              // alpha
+    blas_dev(ctx, B_AXPYZ_NORM, p0, np, {&v, &r, &s}, st + BS_AXPY, BP_S2);  // s = r - alpha v
     A.apply(s, t, false);
-    res.applies++;
     // <t,s>, |t|^2, <rhat,s>, <rhat,t>: omega, and rho_new = <rhat, s - omega t> before r exists,
     // so the x, r and p updates share one pass over the fields
-    blas(ctx, B_DOT4_TS, p0, np, {&t, &s, &rh}, BlasArgs{}, red);
-    double om_r = red[0] / red[2], om_i = red[1] / red[2];
-    double rn_r = red[3] - (om_r * red[5] - om_i * red[6]);
-    double rn_i = red[4] - (om_r * red[6] + om_i * red[5]);
-    // beta = (rho_new / rho) (alpha / omega)
-    double rr = rho_r * rho_r + rho_i * rho_i;
-    double oo = om_r * om_r + om_i * om_i;
-    if (red[2] == 0.0 || !isfinite(oo) || oo == 0.0 || rr == 0.0) {
-      // keep the half step: y + alpha p has residual s
-      blas(ctx, B_AXPY, p0, np, {&p, &y}, cplx(al_r, al_i));
-      r2 = s2;
-      res.breakdown = true;
-      break;
-    }
-    double q_r = (rn_r * rho_r + rn_i * rho_i) / rr, q_i = (rn_i * rho_r - rn_r * rho_i) / rr;
-    double w_r = (al_r * om_r + al_i * om_i) / oo, w_i = (al_i * om_r - al_r * om_i) / oo;
-    double be_r = q_r * w_r - q_i * w_i, be_i = q_r * w_i + q_i * w_r;
-    blas(ctx, B_BICG_FUSED, p0, np, {&y, &p, &s, &t, &v, &r}, cplx(al_r, al_i, om_r, om_i, be_r, be_i),
-         red);
-    r2 = red[0];
+    blas_dev(ctx, B_DOT4_TS, p0, np, {&t, &s, &rh}, nullptr, BP_OMEGA_ROUNDED);
+    blas_dev(ctx, B_BICG_FUSED, p0, np, {&y, &p, &s, &t, &v, &r}, st + BS_FUSED, BP_R2);
+    res.applies += 2;
+    res.iters++;
+    bicg_state(ctx, S);
+    r2 = S[BS_R2];
     if (!isfinite(r2)) { res.breakdown = true; break; }
     if (r2 < best2) { best2 = r2; best_it = res.iters; }
     if (r2 <= tgt2) { res.converged = true; break; }
-    rho_r = rn_r;
-    rho_i = rn_i;
-    if (rho_r * rho_r + rho_i * rho_i < 1e-60 * bn2 * bn2) {
+    if (S[BS_BREAK] != 0.0) { res.breakdown = true; break; }
+    const double rho2 = S[BS_RHO] * S[BS_RHO] + S[BS_RHO + 1] * S[BS_RHO + 1];
+    if (rho2 < 1e-60 * bn2 * bn2) {
       // rho breakdown: restart the shadow residual
       blas(ctx, B_COPY, p0, np, {&r, &rh});
       blas(ctx, B_COPY, p0, np, {&r, &p});
-      rho_r = r2;
-      rho_i = 0;
+      blas_dev(ctx, B_DOT, p0, np, {&rh, &r}, nullptr, BP_RHO);
       res.restarts++;
     }
   }
@@ -748,7 +723,6 @@ bool bicgstab_reliable(tp_op op, const tp_solve_params& P, const KrylovOp& A, bo
     info.applies += 2;
     info.iters++;
     bicg_state(ctx, S);
-    // a vanishing <rhat, v> makes alpha and everything after it non-finite
     rr2 = S[BS_R2];
     if (S[BS_BREAK] != 0.0 || !isfinite(rr2)) return give_up();
     if (rr2 < seg_best) {

@@ -358,12 +358,12 @@ enum BicgSlot {
   BS_BETA = 6,     // beta = (rho_new / rho) (alpha / omega)
   BS_S2 = 8,       // |s|^2
   BS_R2 = 9,       // |r|^2 after the fused update
-  BS_BREAK = 10,   // nonzero: |t|^2, omega or rho vanished or is not finite
+  BS_BREAK = 10,   // nonzero: <rhat, v>, |t|^2, omega or rho vanished or is not finite
   BS_AXPY = 16,    // coefficients (a, b, c) of s = r - alpha v
   BS_FUSED = 24,   // coefficients (alpha, omega, beta) of the fused update
   BS_COUNT = 32
 };
-enum BicgPost { BP_NONE, BP_RHO, BP_ALPHA, BP_S2, BP_OMEGA, BP_R2 };
+enum BicgPost { BP_NONE, BP_RHO, BP_ALPHA, BP_S2, BP_OMEGA, BP_R2, BP_ALPHA_ROUNDED, BP_OMEGA_ROUNDED };
 
 struct BlasArgs {
   double a[2], b[2], c[2];  // complex coefficients
