@@ -779,10 +779,11 @@ tp_status tp_op_mass(tp_op op, double* mu) {
   });
 }
 
-// FP64 applies that work on the caller's canonical fields directly (k_canon.hip): the same
-// argument checks as apply_wrap.  Returns false, having done nothing, for the calls that go through
-// the internal layout: reduced precisions, and fields that overlap (each input is then packed
-// before any output is written).
+// FP64 applies that work on the caller's canonical fields directly (k_canon.hip, k_line_canon): the
+// same argument checks as apply_wrap.  False for the calls that go through the internal layout:
+// reduced precisions, and fields that overlap (each input is then packed before any output is
+// written).  The schemes' applies and maps go through it too: they are the same operations, bit for
+// bit, as on internal fields.
 static bool canon_direct(tp_op op, int32_t prec, const void* dst, const void* src) {
   if (!op || !dst || !src || prec != TP_F64) return false;
   const uintptr_t d = reinterpret_cast<uintptr_t>(dst), s = reinterpret_cast<uintptr_t>(src);
@@ -795,13 +796,10 @@ static tp_status apply_canon(tp_op op, void* dst, const void* src, bool g5, Site
     launch_site_canon(op, static_cast<const double2*>(src), static_cast<double2*>(dst), g5, cf, clov);
   });
 }
-static tp_status canon_M(tp_op op, void* dst, const void* src, bool dagger) {
-  return apply_canon(op, dst, src, dagger, SiteCoef{op->mu, 1.0, -1.0, -1.0 / op->gf, 0.0},
-                     op->c ? op->c->a4_d : nullptr);
-}
-
 tp_status tp_apply_M(tp_op op, int32_t prec, void* dst, const void* src, int32_t dagger) {
-  if (canon_direct(op, prec, dst, src)) return canon_M(op, dst, src, dagger != 0);
+  if (canon_direct(op, prec, dst, src))
+    return apply_canon(op, dst, src, dagger != 0, SiteCoef{op->mu, 1.0, -1.0, -1.0 / op->gf, 0.0},
+                       op->c ? op->c->a4_d : nullptr);
   return apply_wrap(op, prec, dst, src, false, dagger != 0,
                     [&](Field& a, Field& b) { op_apply_M(op, prec, a, b, false); });
 }
@@ -863,10 +861,6 @@ tp_status tp_apply_prec(tp_op op, int32_t scheme, int32_t prec, void* dst, const
   return guard([&] {
     check_scheme(scheme);
     check_scheme_prec(scheme, prec);
-    if (scheme == TP_UNPREC && canon_direct(op, prec, dst, src)) {
-      if (tp_status st = canon_M(op, dst, src, dagger != 0)) TP_THROW(st, g_last_error);
-      return;
-    }
     // dagger: gamma5 on the way in and out around N (Mt^dagger = gamma5 N gamma5)
     tp_status s = apply_wrap(op, prec, dst, src, scheme_layout4(scheme), dagger != 0,
                              [&](Field& a, Field& b) {
@@ -926,10 +920,6 @@ tp_status tp_prepare_source(tp_op op, int32_t scheme, int32_t prec, void* et, co
   return guard([&] {
     check_scheme(scheme);
     check_scheme_prec(scheme, prec);
-    if (scheme == TP_TEMPORAL && canon_direct(op, prec, et, eta)) {
-      if (tp_status st = line_apply(op, prec, LM_CL, et, eta)) TP_THROW(st, g_last_error);
-      return;
-    }
     tp_status s = apply_wrap(op, prec, et, eta, scheme_layout4(scheme), false,
                              [&](Field& a, Field& b) { op_prepare(op, scheme, prec, a, b); });
     if (s != TP_OK) TP_THROW(s, g_last_error);
@@ -940,10 +930,6 @@ tp_status tp_reconstruct(tp_op op, int32_t scheme, int32_t prec, void* x, const 
   return guard([&] {
     check_scheme(scheme);
     check_scheme_prec(scheme, prec);
-    if (scheme == TP_TEMPORAL && canon_direct(op, prec, x, y)) {
-      if (tp_status st = line_apply(op, prec, LM_CR, x, y)) TP_THROW(st, g_last_error);
-      return;
-    }
     tp_status s = apply_wrap(op, prec, x, y, scheme_layout4(scheme), false,
                              [&](Field& a, Field& b) { op_reconstruct(op, scheme, prec, a, b); });
     if (s != TP_OK) TP_THROW(s, g_last_error);
