@@ -52,8 +52,8 @@ struct SubSite {
   bool ok;  // false past the lattice's ends: s and t are then those of the last valid site
 };
 inline unsigned sub_blocks(const Lattice& L) { return 2u * unsigned((L.Vs2 + 15) / 16) * unsigned((L.L[3] + 3) / 4); }
-TP_DEV SubSite sub_site(const Geom& g, int lane) {
-  const uint32_t id = xcd_block(blockIdx.x, gridDim.x);
+// The id-th sub-block of the sequence.
+TP_DEV SubSite sub_site_at(const Geom& g, uint32_t id, int lane) {
   const uint32_t blk = id >> 1, nsb = uint32_t(g.Vs2 + 15) / 16;
   const int s = int(blk % nsb) * 16 + (lane & 15), t = int(blk / nsb) * 4 + (lane >> 4);
   SubSite q;
@@ -63,3 +63,5 @@ TP_DEV SubSite sub_site(const Geom& g, int lane) {
   q.t = t < g.Lt ? t : g.Lt - 1;
   return q;
 }
+// That of a workgroup, for launches of one workgroup per sub-block.
+TP_DEV SubSite sub_site(const Geom& g, int lane) { return sub_site_at(g, xcd_block(blockIdx.x, gridDim.x), lane); }
