@@ -810,15 +810,22 @@ struct Shape {
   int CH, NCH, LPB;
 };
 
-// Pick CH (time slices per thread) from `allowed`, NCH = Lt/CH chunks, and LPB lines
-// (a multiple of the 4-line tile) so that LPB * NCH <= max_threads.
-Shape pick_shape(int Lt, int lpb_target, int max_threads, std::initializer_list<int> allowed) {
+// Pick CH (time slices per thread) from `allowed`, NCH = Lt/CH chunks, and LPB lines per
+// workgroup: a multiple of the 4-line tile (and at most 16) with LPB * NCH <= max_threads, the
+// smallest with 128 threads or more.  A line's scan waits at a barrier for the other lines of its
+// workgroup and its registers are held until the last of them ends, so small workgroups fill the
+// CUs better, on small lattices most of all, where large ones leave CUs idle.  As many lines as
+// fit (up to 16) and this, in us: FP32 k_ilu_mid 12^3x64 30.9 and 15.5, 24^3x48 70.7 and 54.2,
+// 24^3x107 377 and 230, 24^3x128 163 and 146, 32^3x64 193 and 154, and C_L there 50.4 and 51.1;
+// FP16 24^3x107 325 and 165; FP64 12^3x64 29.0 and 23.7, 24^3x107 440 and 442, 32^3x64 367 and
+// 338.  One wavefront would do for T = 16, but 4^3x16 lines (FP32) then take 4.8 instead of 4.3.
+Shape pick_shape(int Lt, int max_threads, std::initializer_list<int> allowed) {
   for (int ch : allowed) {
     if (Lt % ch) continue;
     int nch = Lt / ch;
     if (nch * kTile > max_threads) continue;
-    int lpb = lpb_target;
-    while (lpb > kTile && lpb * nch > max_threads) lpb >>= 1;
+    int lpb = kTile;
+    while (lpb < 16 && lpb * nch < 128) lpb <<= 1;
     return Shape{ch, nch, lpb};
   }
   TP_THROW(TP_EDIMS, "time extent not supported by the line kernels");
@@ -907,7 +914,7 @@ void line_t(tp_op op, int par, const LineIO& io, Field& dst) {
   a.nr = dst.nr;
   a.c_out = io.c_out;
   a.c_base = io.c_base;
-  Shape sh = pick_shape(op->g->ctx->lat.L[3], 16, max_threads<S>(), {1, 2, 4});
+  Shape sh = pick_shape(op->g->ctx->lat.L[3], max_threads<S>(), {1, 2, 4});
   if (io.base) {
     if (io.pass) { TP_CH_DISPATCH(sh.CH, go<S>(op, k_line<S, CH, MODE, true, true>, a, sh)) }
     else { TP_CH_DISPATCH(sh.CH, go<S>(op, k_line<S, CH, MODE, true, false>, a, sh)) }
@@ -935,9 +942,7 @@ void line_canon_t(tp_op op, const double2* src, double2* dst) {
   const Lattice& L = ctx->lat;
   LineArgs<double2> a = base_args<double2>(op, 0);
   a.nr = 1;
-  Shape sh = pick_shape(L.L[3], 16, 512, {1, 2, 4});
-  // fewer lines per workgroup while there are less than two workgroups per CU
-  while (sh.LPB > kTile && 2 * ((L.Vs2 + sh.LPB - 1) / sh.LPB) < 512) sh.LPB >>= 1;
+  const Shape sh = pick_shape(L.L[3], 512, {1, 2, 4});
   a.LPB = sh.LPB;
   a.NCH = sh.NCH;
   a.f = pow(op->mu, -double(sh.CH));
@@ -965,7 +970,7 @@ void mid_t(tp_op op, const Field& psi, const Field& u, Field& chi, Field& n) {
   for (int ch : {1, 2, 4}) {
     const int mt = std::min(max_threads<S>(), ch == 1 ? mid_threads<1>() : mid_threads<2>());
     if (Lt % ch || (Lt / ch) * kTile > mt) continue;
-    sh = pick_shape(Lt, 16, mt, {ch});
+    sh = pick_shape(Lt, mt, {ch});
     break;
   }
   if (sh.CH == 0) TP_THROW(TP_EDIMS, "time extent not supported by the line kernels");

@@ -154,3 +154,21 @@ def test_reductions_around_the_ticket_limit(dims, prec):
             assert float((g.apply_M(xs[k]) - etas[k]).norm() / etas[k].norm()) < 1.05e-10
             assert infos[k]["true_rel_resid"] <= 1e-10
     g.close()
+
+
+# the line kernels take 16 lines a workgroup below 16 chunks of the line, 8 below 32 and 4 from
+# there; 12 and 60 lines of a parity leave a workgroup part empty
+TOL_LINES = {"F64": TOL64, "F32": 2e-5, "F16N": 1.5e-2}  # composites
+
+
+@pytest.mark.parametrize("dims", [(6, 2, 2, 14), (6, 2, 2, 16), (10, 6, 2, 15), (10, 6, 2, 30), (6, 2, 2, 32), (10, 6, 2, 34)])
+@pytest.mark.parametrize("prec", ["F64", "F32", "F16N"])
+def test_lines_per_workgroup(dims, prec):
+    U, o, g = _make(dims)
+    etas = [synth.make_source(dims, 2106 + k) for k in range(2)]
+    f = g.to_field(torch.stack([torch.from_numpy(e).cuda() for e in etas]), "P3", prec)
+    for scheme in ("TEMPORAL_SCHUR", "TEMPORAL"):
+        y = g.from_field(g.apply_prec_field(f, scheme))
+        for k, e in enumerate(etas):
+            assert _rel(y[k], o.prec(scheme, e)) < TOL_LINES[prec], (scheme, k)
+    g.close()
