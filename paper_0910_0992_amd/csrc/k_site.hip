@@ -143,6 +143,93 @@ __global__ void __launch_bounds__(kBlock) k_site_p3(SiteArgsP3<S> a) {
   }
 }
 
+// The same for launches too small to fill the card, one wavefront per hop: wavefront 0 holds the
+// output sites (64 a workgroup) with the terms of the site itself, wavefronts 1..6 bring the six
+// spatial hops' half spinors to LDS, two more the time hops'; wavefront 0 then adds them in
+// k_site_p3's order, so that the results are the same bits.
+template <bool DT> constexpr int split_waves() { return DT ? 9 : 7; }
+
+template <typename S, bool DT, int DS, bool CLOV, bool IN2>
+__global__ void __launch_bounds__(64 * split_waves<DT>()) k_site_split(SiteArgsP3<S> a) {
+  using R = typename Prec<S>::R;
+  using Lt = typename Prec<S>::L;
+  __shared__ cx<R> hop[(split_waves<DT>() - 1) * 6 * 64];
+  const int p = a.par;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t nr = uint32_t(a.nr), id = xcd_block(blockIdx.x, gridDim.x);
+  const uint32_t rhs = id % nr, V2 = uint32_t(a.g.V2);
+  const uint32_t at = id / nr * 64 + uint32_t(lane);
+  const uint32_t i = at < V2 ? at : V2 - 1;  // lanes past the end repeat the last site, unstored
+  int t, s;
+  p3_ts32(a.g, i, t, s);
+  cx<R> out[12], e[12];
+  if (wave == 0) {
+    const SpinorF<S> self = rhs_view(a.self[p], rhs);
+    if constexpr (IN2) load_spinor<S, R>(rhs_view(a.in2[p], rhs), i, e);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) out[c] = czero<R>();
+    if (a.c_mu != 0.0 || CLOV) {
+      cx<R> psi[12];
+      load_spinor<S, R>(self, i, psi);
+      R cm = R(a.c_mu);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) out[c] = cm * psi[c];
+      if constexpr (CLOV) {
+        cx<R> ap[12];
+        clover_apply<R, Lt>(a.clov[p], a.g.V2, i, psi, ap);
+        R ca = R(a.c_A);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) out[c] += ca * ap[c];
+      }
+    }
+  } else {
+    cx<R> w[6];
+    const SpinorF<S> nb = rhs_view(a.nb[p], rhs);
+    const HopIdx x = hop_idx(a.g, p, t, s);
+    switch (wave) {
+      case 1: hop_half<0, true, S, R, Lt, DS>(nb, x.j[0], a.u[p][0], i, w); break;
+      case 2: hop_half<0, false, S, R, Lt, DS>(nb, x.j[1], a.u[1 - p][0], x.j[1], w); break;
+      case 3: hop_half<1, true, S, R, Lt, DS>(nb, x.j[2], a.u[p][1], i, w); break;
+      case 4: hop_half<1, false, S, R, Lt, DS>(nb, x.j[3], a.u[1 - p][1], x.j[3], w); break;
+      case 5: hop_half<2, true, S, R, Lt, DS>(nb, x.j[4], a.u[p][2], i, w); break;
+      case 6: hop_half<2, false, S, R, Lt, DS>(nb, x.j[5], a.u[1 - p][2], x.j[5], w); break;
+      default:
+        if constexpr (DT) hop_time_half<S, R, Lt>(rhs_view(a.self[p], rhs), a.u[p][3], a.g, t, s, wave == 7, w);
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) hop[((wave - 1) * 6 + c) * 64 + lane] = w[c];
+  }
+  __syncthreads();
+  if (wave != 0 || at >= V2) return;
+  auto take = [&](int h, cx<R>* w) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) w[c] = hop[(h * 6 + c) * 64 + lane];
+  };
+  cx<R> w[6];
+  if constexpr (DT) {
+    const R ct = R(a.c_t);
+    take(6, w);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) out[6 + c] += ct * w[c];
+    take(7, w);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) out[c] += ct * w[c];
+  }
+  const R cs = R(0.5 * a.c_s);
+  take(0, w); recon_minus<0, R>(out, w, cs);
+  take(1, w); recon_plus<0, R>(out, w, cs);
+  take(2, w); recon_minus<1, R>(out, w, cs);
+  take(3, w); recon_plus<1, R>(out, w, cs);
+  take(4, w); recon_minus<2, R>(out, w, cs);
+  take(5, w); recon_plus<2, R>(out, w, cs);
+  if constexpr (IN2) {
+    R ci = R(a.c_in);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) out[c] += ci * e[c];
+  }
+  store_spinor<S, R>(rhs_view(a.dst[p], rhs), i, out);
+}
+
 // ---- 4D even-odd Schur (p4 layout) ---------------------------------------------------------
 template <typename S>
 struct ArgsP4 {
@@ -245,12 +332,29 @@ template <> const __half2* clover_base<__half2>(tp_op op, int kind, bool l4) {
   return nullptr;
 }
 
+// Up to two workgroups of k_site_split a CU (64 sites each): k_site_p3 has less than one wavefront
+// a SIMD there and waits for one hop after another.  k_site_p3 and k_site_split, D_s alone / with the
+// clover term, in us: FP64 4^3x16 9.1 / 10.4 and 5.0 / 5.2, 8^3x64 12.2 / 14.0 and 6.8 / 7.4,
+// 10^3x64 15.6 / 18.0 and 9.9 / 14.2, 12x12x8x64 14.2 / 17.4 and 12.2 / 17.7, 12^3x64 15.4 / 20.4
+// and 15.1 / 24.1; FP32 (alone) 6.1 and 4.6, 10^3x64 9.1 and 6.1, 12^3x64 9.7 and 9.1, 16^3x64 14.1
+// and 15.8; FP16 6.0 / 6.8 and 4.7 / 4.4, 10^3x64 7.9 / 8.7 and 5.7 / 5.7, 16^3x64 12.2 / 14.0 and
+// 13.3 / 16.1.  Not with a fused norm, whose partial sums are k_site_p3's.
+constexpr int64_t kSplitSites = 1 << 15;
+
 template <typename S, bool DT, int DS, bool CLOV, bool IN2, bool NORM>
 void site_go(tp_op op, SiteArgsP3<S> a, int64_t nblocks, int par0, int npar) {
   tp_ctx ctx = op->g->ctx;
   for (int q = 0; q < npar; ++q) {
     a.par = par0 + q;
     a.partial = ctx->red_partial + (int64_t)q * nblocks * 8;
+    if constexpr (DS != 0 && !NORM) {
+      if (a.g.V2 * a.nr <= kSplitSites) {
+        hipLaunchKernelGGL((k_site_split<S, DT, DS, CLOV, IN2>), dim3(unsigned((a.g.V2 + 63) / 64 * a.nr)),
+                           dim3(64 * split_waves<DT>()), 0, ctx->stream, a);
+        LAUNCH_CHECK();
+        continue;
+      }
+    }
     hipLaunchKernelGGL((k_site_p3<S, DT, DS, CLOV, IN2, NORM>), dim3((unsigned)(nblocks * a.nr)), dim3(kBlock),
                        0, ctx->stream, a);
     LAUNCH_CHECK();

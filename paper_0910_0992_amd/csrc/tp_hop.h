@@ -6,47 +6,66 @@
 
 #include "tp_device.h"
 
-// out += c * D_t psi at p3 site (t, s); psi and the links live on the same parity.
-// In the Dirac-Pauli basis P- = lower spins, P+ = upper spins.
+// The transported half spinor of one time hop at p3 site (t, s); psi and the links live on the same
+// parity.  In the Dirac-Pauli basis P- = lower spins, P+ = upper spins.
+template <typename S, typename R, typename Lt>
+TP_DEV void hop_time_half(const SpinorF<S>& f, const LinkF<Lt>& ut, const Geom& g, int t, int s, bool fwd,
+                          cx<R>* w) {
+  cx<R> v[6];
+  if (fwd) {
+    load_half<S, R>(f, 1, p3_idx32(g, t + 1 == g.Lt ? 0 : t + 1, s), v);
+    su3<R> U = load_su3<R, Lt>(ut, p3_idx32(g, t, s));
+    mv(U, v, w);
+    mv(U, v + 3, w + 3);
+  } else {
+    const uint32_t jb = p3_idx32(g, t == 0 ? g.Lt - 1 : t - 1, s);
+    load_half<S, R>(f, 0, jb, v);
+    su3<R> V = load_su3<R, Lt>(ut, jb);
+    mvd(V, v, w);
+    mvd(V, v + 3, w + 3);
+  }
+}
+
+// out += c * D_t psi at p3 site (t, s).
 template <typename S, typename R, typename Lt>
 TP_DEV void hop_time_p3(const SpinorF<S>& f, const LinkF<Lt>& ut, const Geom& g, int t, int s, R c,
                         cx<R>* out) {
-  int tf = t + 1 == g.Lt ? 0 : t + 1;
-  int tb = t == 0 ? g.Lt - 1 : t - 1;
-  const uint32_t i = p3_idx32(g, t, s);
-  const uint32_t jf = p3_idx32(g, tf, s), jb = p3_idx32(g, tb, s);
-  cx<R> v[6], w[6];
-  load_half<S, R>(f, 1, jf, v);
-  su3<R> U = load_su3<R, Lt>(ut, i);
-  mv(U, v, w);
-  mv(U, v + 3, w + 3);
+  cx<R> w[6];
+  hop_time_half<S, R, Lt>(f, ut, g, t, s, true, w);
 #pragma unroll
   for (int k = 0; k < 6; ++k) out[6 + k] += c * w[k];
-  load_half<S, R>(f, 0, jb, v);
-  su3<R> V = load_su3<R, Lt>(ut, jb);
-  mvd(V, v, w);
-  mvd(V, v + 3, w + 3);
+  hop_time_half<S, R, Lt>(f, ut, g, t, s, false, w);
 #pragma unroll
   for (int k = 0; k < 6; ++k) out[k] += c * w[k];
 }
 
-// One spatial direction K of the projected hop; c already includes the 1/2 of P+-.
+// One projected hop: the transported half spinor w, from the neighbour at j and the link at il
+// (forward: of this site, applied; backward: of the neighbour, its dagger applied).
 // ROWS: stored rows of the links (2 = SU(3), third row rebuilt).
+template <int K, bool FWD, typename S, typename R, typename Lt, int ROWS>
+TP_DEV void hop_half(const SpinorF<S>& nb, uint32_t j, const LinkF<Lt>& u, uint32_t il, cx<R>* w) {
+  cx<R> psi[12], h[6];
+  load_spinor<S, R>(nb, j, psi);
+  if constexpr (FWD) proj_minus<K, R>(psi, h);
+  else proj_plus<K, R>(psi, h);
+  su3<R> U = load_su3<R, Lt, ROWS>(u, il);
+  if constexpr (FWD) {
+    mv(U, h, w);
+    mv(U, h + 3, w + 3);
+  } else {
+    mvd(U, h, w);
+    mvd(U, h + 3, w + 3);
+  }
+}
+
+// One spatial direction K of the projected hop; c already includes the 1/2 of P+-.
 template <int K, typename S, typename R, typename Lt, int ROWS = 3>
 TP_DEV void hop_dir(const SpinorF<S>& nb, const LinkF<Lt>& u_fwd, uint32_t i_fwd_link,
                     uint32_t jf, const LinkF<Lt>& u_bwd, uint32_t jb, R c, cx<R>* out) {
-  cx<R> psi[12], h[6], w[6];
-  load_spinor<S, R>(nb, jf, psi);
-  proj_minus<K, R>(psi, h);
-  su3<R> U = load_su3<R, Lt, ROWS>(u_fwd, i_fwd_link);
-  mv(U, h, w);
-  mv(U, h + 3, w + 3);
+  cx<R> w[6];
+  hop_half<K, true, S, R, Lt, ROWS>(nb, jf, u_fwd, i_fwd_link, w);
   recon_minus<K, R>(out, w, c);
-  load_spinor<S, R>(nb, jb, psi);
-  proj_plus<K, R>(psi, h);
-  su3<R> V = load_su3<R, Lt, ROWS>(u_bwd, jb);
-  mvd(V, h, w);
-  mvd(V, h + 3, w + 3);
+  hop_half<K, false, S, R, Lt, ROWS>(nb, jb, u_bwd, jb, w);
   recon_plus<K, R>(out, w, c);
 }
 

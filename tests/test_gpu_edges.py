@@ -172,3 +172,21 @@ def test_lines_per_workgroup(dims, prec):
         for k, e in enumerate(etas):
             assert _rel(y[k], o.prec(scheme, e)) < TOL_LINES[prec], (scheme, k)
     g.close()
+
+
+# one wavefront per hop up to 32768 sites of a parity times right-hand sides, one thread per site
+# beyond; 64 sites a workgroup, the last one part empty
+@pytest.mark.parametrize("dims,nr", [((2, 2, 2, 3), 1), ((6, 2, 2, 9), 5), ((8, 8, 8, 43), 3), ((8, 8, 8, 42), 3), ((8, 8, 8, 128), 1),
+                                     ((8, 8, 8, 130), 1)])
+@pytest.mark.parametrize("prec", ["F64", "F32", "F16N"])
+def test_site_kernels_around_the_split(dims, nr, prec):
+    big = np.prod(dims) > 10000
+    U, o, g = _make(dims, bc=1)
+    etas = [synth.make_source(dims, 2108 + k) for k in range(nr)]
+    f = g.to_field(torch.stack([torch.from_numpy(e).cuda() for e in etas]), "P3", prec)
+    for scheme, dagger in (("UNPREC", False), ("UNPREC", True), ("TEMPORAL_SCHUR", False)):
+        y = g.from_field(g.apply_prec_field(f, scheme, dagger))
+        for k in range(0, nr, 2 if big else 1):
+            ref = (o.prec_dag if dagger else o.prec)(scheme, etas[k])
+            assert _rel(y[k], ref) < TOL_LINES[prec], (scheme, dagger, k)
+    g.close()
