@@ -23,34 +23,34 @@ METRIC = "time-to-solution @1e-10 resid (mixed vs FP64 even-odd); operator HBM G
 HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per launch, from rocprofv3 FETCH_SIZE + WRITE_SIZE runs scaled by a 1 GiB copy
-# (FETCH x1.9999, WRITE x1.0000; the runs and their commands are summarised in
+# (FETCH x2.0000, WRITE x1.0000; the runs and their commands are summarised in
 # profiles/hbm_traffic_clover_32x256.md), for the kernel sources whose hash is recorded; any
 # change to those sources makes the figure stale and it is reported as null.
 TRAFFIC = {
     ("clover_32x256", "F16N", "ilu_mid"): {
         "bytes_per_launch": 1.5486e+09,
         "sources": ["k_line_impl.h", "k_line_f16.hip", "k_line.hip", "tp_device.h"],
-        "sha256": "03da316c1837240dac89de534cfcf376d9d81eb1b76a8768aae687375421c936",
+        "sha256": "e4e82d73bf07cecaaf8bc165b14485db4e432c40abe7333b9aaab6574c6ed081",
     },
     ("clover_32x256", "F16N", "hop_clover"): {
-        "bytes_per_launch": 2.6941e+09,
+        "bytes_per_launch": 2.6816e+09,
         "sources": ["k_site.hip", "tp_hop.h", "tp_device.h"],
-        "sha256": "f3ee06be1968e6749e6d2c7fb0f86e78ee848cf435851b269700937e959e3e9b",
+        "sha256": "d18bafc7974e8dfdbfc7b3bd865e54ef966085d828cb9834190d4dafef9ff27e",
     },
     ("clover_32x256", "F16N", "hop_ds"): {
-        "bytes_per_launch": 1.6844e+09,
+        "bytes_per_launch": 1.6863e+09,
         "sources": ["k_site.hip", "tp_hop.h", "tp_device.h"],
-        "sha256": "f3ee06be1968e6749e6d2c7fb0f86e78ee848cf435851b269700937e959e3e9b",
+        "sha256": "d18bafc7974e8dfdbfc7b3bd865e54ef966085d828cb9834190d4dafef9ff27e",
     },
     ("clover_32x256", "F16N", "blas_bicg_fused"): {
         "bytes_per_launch": 3.7582e+09,
         "sources": ["k_blas.hip", "tp_device.h"],
-        "sha256": "88035dcc81646db7be2d2dc697b7cbf54b915edb3ca7d9a5470709df7449e16a",
+        "sha256": "68235116c321e6ff0aded0b254187495fa7107cc206b6c846ec0fc7f92137da6",
     },
     ("clover_32x256", "F16N", "scan_cl"): {
         "bytes_per_launch": 7.0949e+08,
         "sources": ["k_line_impl.h", "k_line_f16.hip", "k_line.hip", "tp_device.h"],
-        "sha256": "03da316c1837240dac89de534cfcf376d9d81eb1b76a8768aae687375421c936",
+        "sha256": "e4e82d73bf07cecaaf8bc165b14485db4e432c40abe7333b9aaab6574c6ed081",
     },
 }
 

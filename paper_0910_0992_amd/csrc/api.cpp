@@ -195,7 +195,8 @@ Field field_alloc(tp_ctx ctx, int prec, int nr) {
   // Large fields start at different offsets of their (alike aligned) allocations: the level-1
   // kernels stream up to six fields at the same index, and where the fields lie a power of two
   // apart those streams meet in the same memory channels and banks.  The fused BiCGStab update at
-  // 32^3x256 (F16N) took 640 to 750 us from one process to the next without, 645 us with.
+  // 32^3x256 (F16N) took 670 to 750 us from one process to the next without, 640 to 675 us beside it
+  // with (735 us on another card).
   constexpr size_t kSkew = 17 * 256, kSkews = 16, kLarge = size_t(8) << 20;
   const size_t skew = db >= kLarge ? kSkew * (ctx->fields_made++ % kSkews) : 0;
   f.base = dev_alloc(ctx, db + (db >= kLarge ? kSkew * kSkews : 0));
