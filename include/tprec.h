@@ -129,8 +129,9 @@ tp_status tp_ctx_set_allocator(tp_ctx ctx, tp_alloc_fn alloc_fn, tp_free_fn free
 tp_status tp_ctx_device_bytes(tp_ctx ctx, size_t* bytes);
 
 /* ---- gauge field ------------------------------------------------------------
- * Copies the canonical links (host or device pointer, per `where`) into the
- * library's layouts and prepares the per-time-line products used by T^-1:
+ * Copies the canonical links (host or device pointer, per `where`; device links need not
+ * lie on the context's device) into the library's layouts and prepares the per-time-line
+ * products used by T^-1:
  * W(t) = U_t(t) U_t(t+1) ... U_t(Lt-1) with the boundary phase folded into the
  * last link; W(0) is the Polyakov loop (Sec. II.A, the closed form of X).
  * Time links must be unitary (checked to 1e-10, else TP_EINVAL): the p3 operators

@@ -82,7 +82,7 @@ class Field:
 class Operator:
     """M = A + mu - D_t - D_s/gamma_f bound to a gauge field, on one GPU.
 
-    links: complex128 tensor [4, Lt, Lz, Ly, Lx, 3, 3] (CPU or CUDA).
+    links: complex128 tensor [4, Lt, Lz, Ly, Lx, 3, 3] (CPU or any CUDA device).
     c_s, c_t: the literal SW coefficients (both 0 for Wilson fermions).
     bc_t: +1 periodic or -1 antiperiodic in time.
     allocator: "torch" (default) hands every device allocation of the library to torch's
@@ -112,7 +112,7 @@ class Operator:
             L.check(lib.tp_ctx_set_allocator(self._ctx, self._alloc_cb[0], self._alloc_cb[1], None))
         elif allocator != "hip":
             raise ValueError(f"allocator {allocator!r}: 'torch' or 'hip'")
-        links = links.contiguous()
+        links = (links.to(self.device) if links.is_cuda else links).contiguous()
         where = L.TP_DEVICE if links.is_cuda else L.TP_HOST
         L.check(lib.tp_gauge_create(self._ctx, C.c_void_p(links.data_ptr()), where,
                                     C.byref(self._gauge)))

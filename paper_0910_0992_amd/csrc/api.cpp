@@ -59,6 +59,16 @@ void need(const void* p, const char* what) {
   if (!p) TP_THROW(TP_EINVAL, std::string("null pointer: ") + what);
 }
 void set_device(tp_ctx ctx) { HIP_CHECK(hipSetDevice(ctx->device)); }
+// Whether p is memory of the context's own device, which its kernels may read.  That of another
+// device, which a copy reaches, need not be mapped on this one.
+bool own_device_memory(tp_ctx ctx, const void* p) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == ctx->device;
+}
 
 // The spin matrices of the Dirac-Pauli basis and the chiral projections of
 // sigma_{mu nu} used to build the clover blocks on the device.
@@ -536,14 +546,17 @@ tp_status tp_gauge_create(tp_ctx ctx, const void* links, int32_t where, tp_gauge
       g->w_d = static_cast<double2*>(dev_alloc(ctx, size_t(2) * 9 * L.V2 * sizeof(double2)));
       g->poly = static_cast<double2*>(dev_alloc(ctx, size_t(2) * 9 * L.Vs2 * sizeof(double2)));
       int* flags = nullptr;
-      double2* staged = nullptr;  // device copy of host links while they are converted
+      // copy on the context's device, while they are converted, of links that lie elsewhere
+      double2* staged = nullptr;
       int hf[4] = {1, 1, 1, 1};
       try {
         flags = static_cast<int*>(dev_alloc(ctx, 4 * sizeof(int)));
         const double2* dl = static_cast<const double2*>(links);
-        if (where == TP_HOST) {
+        if (where == TP_HOST || !own_device_memory(ctx, links)) {
           staged = static_cast<double2*>(dev_alloc(ctx, lb));
-          HIP_CHECK(hipMemcpyAsync(staged, links, lb, hipMemcpyHostToDevice, ctx->stream));
+          HIP_CHECK(hipMemcpyAsync(staged, links, lb,
+                                   where == TP_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
+                                   ctx->stream));
           dl = staged;
         }
         HIP_CHECK(hipMemsetAsync(flags, 0, 4 * sizeof(int), ctx->stream));
