@@ -306,6 +306,8 @@ void ctx_buffers_alloc(tp_ctx c) {
   c->bicg = c->red_result + 8 * kMaxRhs;
   c->red_ticket = reinterpret_cast<unsigned*>(c->bicg + BS_COUNT);
   HIP_CHECK(hipMemsetAsync(c->bicg, 0, sizeof(double) * (kMaxRhs + BS_COUNT), c->stream));
+  // the first reduction may run on another stream, and finds its ticket at zero
+  HIP_CHECK(hipStreamSynchronize(c->stream));
 }
 void ctx_buffers_free(tp_ctx c) {
   dev_free(c, c->red_partial);
@@ -504,7 +506,6 @@ tp_status tp_ctx_set_allocator(tp_ctx ctx, tp_alloc_fn alloc_fn, tp_free_fn free
     ctx->free_fn = free_fn;
     ctx->alloc_user = user;
     ctx_buffers_alloc(ctx);
-    HIP_CHECK(hipStreamSynchronize(ctx->stream));
   });
 }
 
