@@ -5,6 +5,7 @@
 // 32-bit site offset.  Reductions are deterministic: a fixed grid writes per-block
 // partials, one block sums them in a fixed order.
 #include "tp_internal.h"
+#include "tp_bicg.h"
 
 namespace {
 
@@ -15,80 +16,6 @@ constexpr int kBlasBlocks = 1024;
 static_assert(kBlasBlocks <= kRedBlocks, "partials buffer too small");
 
 static_assert(BS_COUNT <= 8 * kMaxRhs, "pinned staging buffer too small for the solver scalars");
-
-// BiCGStab's scalar steps on the device (single right-hand side), from the reduced values v
-// of the op just finished.  alpha = rho / <rhat, v>; a vanishing or non-finite <rhat, v> is flagged,
-// and the iteration goes on as s = r.
-#define TP_BICG_ALPHA                                                                          \
-  const double den = v[0] * v[0] + v[1] * v[1];                                                \
-  const bool bad = den == 0.0 || !isfinite(den);                                               \
-  const double rr = st[BS_RHO], ri = st[BS_RHO + 1];                                           \
-  const double ar = bad ? 0.0 : (rr * v[0] + ri * v[1]) / den;                                 \
-  const double ai = bad ? 0.0 : (ri * v[0] - rr * v[1]) / den;                                 \
-  st[BS_BREAK] = bad ? 1.0 : 0.0;                                                              \
-  st[BS_ALPHA] = ar;                                                                           \
-  st[BS_ALPHA + 1] = ai;                                                                       \
-  st[BS_AXPY] = -ar;                                                                           \
-  st[BS_AXPY + 1] = -ai;                                                                       \
-  for (int q = 2; q < 6; ++q) st[BS_AXPY + q] = 0.0;
-// v = <t, s>, |t|^2, <rhat, s>, <rhat, t>: omega = <t, s> / |t|^2, rho_new = <rhat, s - omega t>,
-// beta = (rho_new / rho) (alpha / omega).  Without a usable omega the update keeps the half step
-// (x += alpha p, r = s).
-#define TP_BICG_OMEGA                                                                          \
-  const double om_r = v[0] / v[2], om_i = v[1] / v[2];                                         \
-  const double rn_r = v[3] - (om_r * v[5] - om_i * v[6]);                                      \
-  const double rn_i = v[4] - (om_r * v[6] + om_i * v[5]);                                      \
-  const double rho_r = st[BS_RHO], rho_i = st[BS_RHO + 1];                                     \
-  const double al_r = st[BS_ALPHA], al_i = st[BS_ALPHA + 1];                                   \
-  const double rr = rho_r * rho_r + rho_i * rho_i, oo = om_r * om_r + om_i * om_i;             \
-  const double q_r = (rn_r * rho_r + rn_i * rho_i) / rr, q_i = (rn_i * rho_r - rn_r * rho_i) / rr; \
-  const double w_r = (al_r * om_r + al_i * om_i) / oo, w_i = (al_i * om_r - al_r * om_i) / oo; \
-  const double be_r = q_r * w_r - q_i * w_i, be_i = q_r * w_i + q_i * w_r;                     \
-  const bool bad = v[2] == 0.0 || !isfinite(oo) || oo == 0.0 || rr == 0.0;                     \
-  if (bad) st[BS_BREAK] = 1.0;                                                                 \
-  st[BS_OMEGA] = om_r;                                                                         \
-  st[BS_OMEGA + 1] = om_i;                                                                     \
-  st[BS_BETA] = be_r;                                                                          \
-  st[BS_BETA + 1] = be_i;                                                                      \
-  st[BS_FUSED] = al_r;                                                                         \
-  st[BS_FUSED + 1] = al_i;                                                                     \
-  st[BS_FUSED + 2] = bad ? 0.0 : om_r;                                                         \
-  st[BS_FUSED + 3] = bad ? 0.0 : om_i;                                                         \
-  st[BS_FUSED + 4] = bad ? 0.0 : be_r;                                                         \
-  st[BS_FUSED + 5] = bad ? 0.0 : be_i;                                                         \
-  st[BS_RHO] = rn_r;                                                                           \
-  st[BS_RHO + 1] = rn_i;
-
-// The FP64 solver's scalars round every product, as the host arithmetic that formed them before
-// did (its iterates stay what they were bit for bit); the mixed solver's may fuse.
-TP_DEV void bicg_alpha_rounded(const double* v, double* st) {
-#pragma clang fp contract(off)
-  TP_BICG_ALPHA
-}
-TP_DEV void bicg_omega_rounded(const double* v, double* st) {
-#pragma clang fp contract(off)
-  TP_BICG_OMEGA
-}
-TP_DEV void bicg_post(int post, const double* v, double* st) {
-  if (post == BP_RHO) {
-    st[BS_RHO] = v[0];
-    st[BS_RHO + 1] = v[1];
-  } else if (post == BP_ALPHA) {
-    TP_BICG_ALPHA
-  } else if (post == BP_ALPHA_ROUNDED) {
-    bicg_alpha_rounded(v, st);
-  } else if (post == BP_S2) {
-    st[BS_S2] = v[0];
-  } else if (post == BP_OMEGA) {
-    TP_BICG_OMEGA
-  } else if (post == BP_OMEGA_ROUNDED) {
-    bicg_omega_rounded(v, st);
-  } else if (post == BP_R2) {
-    st[BS_R2] = v[0];
-  }
-}
-#undef TP_BICG_ALPHA
-#undef TP_BICG_OMEGA
 
 // Sums nblocks rows of partials in a fixed order (the calling workgroup: kBlock threads), writes
 // the sums to result and runs the solver's scalar step on them.  SHARED: the partials come from
@@ -265,10 +192,8 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
     } else if constexpr (OP == B_AXPYZ_NORM) {
       load_half<S, R>(f0, h, i, x);
       load_half<S, R>(f1, h, i, y);
-      for (int c = 0; c < 6; ++c) {
-        y[c] += cmul(A, x[c]);
-        acc[0] += double(norm2(y[c]));
-      }
+      bicg_half<6>(A, x, y);
+      for (int c = 0; c < 6; ++c) acc[0] += double(norm2(y[c]));
       store_half<S, R>(f2, h, i, y);
     } else if constexpr (OP == B_DOT4_TS) {
       nt_load_half<S, R>(f0, h, i, x);  // t
@@ -285,13 +210,8 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
       load_half<S, R>(f2, h, i, z);
       load_half<S, R>(f3, h, i, w);
       load_half<S, R>(f4, h, i, v);
-      const cx<R> BC = cmul(B, C);
-      for (int c = 0; c < 6; ++c) {
-        x[c] += cmul(A, y[c]) + cmul(B, z[c]);
-        z[c] = z[c] - cmul(B, w[c]);                  // r = s - omega t
-        y[c] = z[c] + cmul(C, y[c]) - cmul(BC, v[c]);  // p = r + beta (p - omega v)
-        acc[0] += double(norm2(z[c]));
-      }
+      bicg_full<6>(A, B, C, x, y, z, w, v);
+      for (int c = 0; c < 6; ++c) acc[0] += double(norm2(z[c]));
       store_half<S, R>(f0, h, i, x);
       store_half<S, R>(f5, h, i, z);
       store_half<S, R>(f1, h, i, y);
