@@ -4,8 +4,8 @@
 // indices uniform across the grid, so every plane address is a uniform base plus a
 // 32-bit site offset.  Reductions are deterministic: a fixed grid writes per-block
 // partials, one block sums them in a fixed order.
-#include "tp_internal.h"
 #include "tp_bicg.h"
+#include "tp_internal.h"
 
 namespace {
 
@@ -103,7 +103,7 @@ struct BlasK {
   int nr;                      // right-hand sides: block b works on field b % nr of each batch
   double coef[kMaxRhs][8];     // nr > 1: per right-hand side a, b, c (complex) and a skip flag
   double* partial;             // [nr][blocks per right-hand side][8]
-  const double* dcoef;         // single right-hand side: a, b, c read from device memory
+  const double* dcoef;         // single right-hand side: a, b, c and the flag read from device memory
   Finish fin;
 };
 template <typename R> TP_DEV cx<R> cc(const double* z) { return cx<R>{R(z[0]), R(z[1])}; }
@@ -145,7 +145,8 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
     C = cc<R>(k.c);
   }
   // a skipped right-hand side is left untouched
-  const int npar = (nr > 1 && k.coef[rhs][6] != 0.0) ? 0 : k.npar;
+  const bool skip = k.dcoef ? k.dcoef[6] != 0.0 : nr > 1 && k.coef[rhs][6] != 0.0;
+  const int npar = skip ? 0 : k.npar;
   for (int q = 0; q < npar; ++q)
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -192,8 +193,10 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
     } else if constexpr (OP == B_AXPYZ_NORM) {
       load_half<S, R>(f0, h, i, x);
       load_half<S, R>(f1, h, i, y);
-      bicg_half<6>(A, x, y);
-      for (int c = 0; c < 6; ++c) acc[0] += double(norm2(y[c]));
+      for (int c = 0; c < 6; ++c) {
+        y[c] += cmul(A, x[c]);
+        acc[0] += double(norm2(y[c]));
+      }
       store_half<S, R>(f2, h, i, y);
     } else if constexpr (OP == B_DOT4_TS) {
       nt_load_half<S, R>(f0, h, i, x);  // t
@@ -210,8 +213,13 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
       load_half<S, R>(f2, h, i, z);
       load_half<S, R>(f3, h, i, w);
       load_half<S, R>(f4, h, i, v);
-      bicg_full<6>(A, B, C, x, y, z, w, v);
-      for (int c = 0; c < 6; ++c) acc[0] += double(norm2(z[c]));
+      const cx<R> BC = cmul(B, C);
+      for (int c = 0; c < 6; ++c) {
+        x[c] += cmul(A, y[c]) + cmul(B, z[c]);
+        z[c] = z[c] - cmul(B, w[c]);                  // r = s - omega t
+        y[c] = z[c] + cmul(C, y[c]) - cmul(BC, v[c]);  // p = r + beta (p - omega v)
+        acc[0] += double(norm2(z[c]));
+      }
       store_half<S, R>(f0, h, i, x);
       store_half<S, R>(f5, h, i, z);
       store_half<S, R>(f1, h, i, y);

@@ -472,8 +472,7 @@ KrylovResult bicgstab(const KrylovOp& A, const Field& b, Field& y, double eps, i
     return res;
   }
   // scalars stay on the device and the host reads them once per iteration (see
-  // bicgstab_reliable); an iteration always runs to its end, which keeps the half step when
-  // its second half breaks down
+  // bicgstab_reliable); an iteration always runs to its end
   double* st = ctx->bicg;
   double S[BS_COUNT];
   blas_dev(ctx, B_DOT, p0, np, {&rh, &r}, nullptr, BP_RHO);
@@ -495,14 +494,22 @@ KrylovResult bicgstab(const KrylovOp& A, const Field& b, Field& y, double eps, i
     // so the x, r and p updates share one pass over the fields
     blas_dev(ctx, B_DOT4_TS, p0, np, {&t, &s, &rh}, nullptr, BP_OMEGA_ROUNDED);
     blas_dev(ctx, B_BICG_FUSED, p0, np, {&y, &p, &s, &t, &v, &r}, st + BS_FUSED, BP_R2);
-    res.applies += 2;
-    res.iters++;
     bicg_state(ctx, S);
+    res.applies += 2;
+    if (S[BS_BREAK] != BRK_ALPHA) res.iters++;
+    if (S[BS_BREAK] != BRK_NONE) {
+      if (S[BS_BREAK] == BRK_OMEGA) {  // keep the half step: y + alpha p has residual s
+        blas(ctx, B_AXPY, p0, np, {&p, &y}, cplx(S[BS_ALPHA], S[BS_ALPHA + 1]));
+        r2 = S[BS_S2];
+      }
+      res.converged = r2 <= tgt2;
+      res.breakdown = !res.converged;
+      break;
+    }
     r2 = S[BS_R2];
     if (!isfinite(r2)) { res.breakdown = true; break; }
     if (r2 < best2) { best2 = r2; best_it = res.iters; }
     if (r2 <= tgt2) { res.converged = true; break; }
-    if (S[BS_BREAK] != 0.0) { res.breakdown = true; break; }
     const double rho2 = S[BS_RHO] * S[BS_RHO] + S[BS_RHO + 1] * S[BS_RHO + 1];
     if (rho2 < 1e-60 * bn2 * bn2) {
       // rho breakdown: restart the shadow residual
@@ -724,7 +731,7 @@ bool bicgstab_reliable(tp_op op, const tp_solve_params& P, const KrylovOp& A, bo
     info.iters++;
     bicg_state(ctx, S);
     rr2 = S[BS_R2];
-    if (S[BS_BREAK] != 0.0 || !isfinite(rr2)) return give_up();
+    if (S[BS_BREAK] != BRK_NONE || !isfinite(rr2)) return give_up();
     if (rr2 < seg_best) {
       seg_best = rr2;
       seg_best_it = info.iters;

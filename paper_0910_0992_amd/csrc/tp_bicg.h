@@ -1,26 +1,24 @@
-// BiCGStab's steps: the scalar ones between its reductions, and what its vector updates do to the
-// elements of a half spinor.
+// BiCGStab's scalar steps on the device (single right-hand side), from the reduced values v of the op
+// just finished.  An iteration runs to its end whatever they find; one that breaks down is flagged
+// (BS_BREAK) and skips its update of x, r and p, so that the host can end it from what they were.
 #pragma once
 #include "tp_internal.h"
 
-// The scalar steps on the device (single right-hand side), from the reduced values v of the op
-// just finished.  alpha = rho / <rhat, v>; with a vanishing or non-finite <rhat, v> the
-// iteration is flagged, alpha and omega are zero and its updates leave x and r as they are.
+// alpha = rho / <rhat, v>, unless <rhat, v> vanishes or is not finite (BRK_ALPHA).
 #define TP_BICG_ALPHA                                                                          \
   const double den = v[0] * v[0] + v[1] * v[1];                                                \
-  const bool bad = den == 0.0 || !__builtin_isfinite(den);                                               \
+  const bool bad = den == 0.0 || !__builtin_isfinite(den);                                     \
   const double rr = st[BS_RHO], ri = st[BS_RHO + 1];                                           \
   const double ar = bad ? 0.0 : (rr * v[0] + ri * v[1]) / den;                                 \
   const double ai = bad ? 0.0 : (ri * v[0] - rr * v[1]) / den;                                 \
-  st[BS_BREAK] = bad ? 1.0 : 0.0;                                                              \
+  st[BS_BREAK] = bad ? BRK_ALPHA : BRK_NONE;                                                   \
   st[BS_ALPHA] = ar;                                                                           \
   st[BS_ALPHA + 1] = ai;                                                                       \
   st[BS_AXPY] = -ar;                                                                           \
   st[BS_AXPY + 1] = -ai;                                                                       \
-  for (int q = 2; q < 6; ++q) st[BS_AXPY + q] = 0.0;
+  for (int q = 2; q < 7; ++q) st[BS_AXPY + q] = 0.0;
 // v = <t, s>, |t|^2, <rhat, s>, <rhat, t>: omega = <t, s> / |t|^2, rho_new = <rhat, s - omega t>,
-// beta = (rho_new / rho) (alpha / omega).  Without a usable omega the update keeps the half step
-// (omega = 0: x += alpha p, r = s).
+// beta = (rho_new / rho) (alpha / omega), unless there is no usable omega (BRK_OMEGA).
 #define TP_BICG_OMEGA                                                                          \
   const double om_r = v[0] / v[2], om_i = v[1] / v[2];                                         \
   const double rn_r = v[3] - (om_r * v[5] - om_i * v[6]);                                      \
@@ -31,18 +29,15 @@
   const double q_r = (rn_r * rho_r + rn_i * rho_i) / rr, q_i = (rn_i * rho_r - rn_r * rho_i) / rr; \
   const double w_r = (al_r * om_r + al_i * om_i) / oo, w_i = (al_i * om_r - al_r * om_i) / oo; \
   const double be_r = q_r * w_r - q_i * w_i, be_i = q_r * w_i + q_i * w_r;                     \
-  const bool bad = st[BS_BREAK] != 0.0 || v[2] == 0.0 || !__builtin_isfinite(oo) || oo == 0.0 || rr == 0.0; \
-  if (bad) st[BS_BREAK] = 1.0;                                                                 \
-  st[BS_OMEGA] = om_r;                                                                         \
-  st[BS_OMEGA + 1] = om_i;                                                                     \
-  st[BS_BETA] = be_r;                                                                          \
-  st[BS_BETA + 1] = be_i;                                                                      \
+  const bool bad = v[2] == 0.0 || !__builtin_isfinite(oo) || oo == 0.0 || rr == 0.0;           \
+  if (bad && st[BS_BREAK] == BRK_NONE) st[BS_BREAK] = BRK_OMEGA;                               \
   st[BS_FUSED] = al_r;                                                                         \
   st[BS_FUSED + 1] = al_i;                                                                     \
-  st[BS_FUSED + 2] = bad ? 0.0 : om_r;                                                         \
-  st[BS_FUSED + 3] = bad ? 0.0 : om_i;                                                         \
-  st[BS_FUSED + 4] = bad ? 0.0 : be_r;                                                         \
-  st[BS_FUSED + 5] = bad ? 0.0 : be_i;                                                         \
+  st[BS_FUSED + 2] = om_r;                                                                     \
+  st[BS_FUSED + 3] = om_i;                                                                     \
+  st[BS_FUSED + 4] = be_r;                                                                     \
+  st[BS_FUSED + 5] = be_i;                                                                     \
+  st[BS_FUSED + 6] = st[BS_BREAK];                                                             \
   st[BS_RHO] = rn_r;                                                                           \
   st[BS_RHO + 1] = rn_i;
 
@@ -76,27 +71,3 @@ TP_HD void bicg_post(int post, const double* v, double* st) {
 }
 #undef TP_BICG_ALPHA
 #undef TP_BICG_OMEGA
-
-// The updates of N elements.  A coefficient of zero leaves its term out, whatever the vector holds:
-// an iteration that breaks down has such coefficients, and its v, t or s need not be finite (its p is
-// not used again).
-template <typename R> TP_HD bool is_zero(cx<R> a) { return a.re == R(0) && a.im == R(0); }
-template <typename R> TP_HD cx<R> unless(bool out, cx<R> v) { return out ? czero<R>() : v; }
-// s = r + a v (a = -alpha), into r
-template <int N, typename R> TP_HD void bicg_half(cx<R> a, const cx<R>* v, cx<R>* r) {
-  const bool out = is_zero(a);
-#pragma unroll
-  for (int c = 0; c < N; ++c) r[c] += cmul(a, unless(out, v[c]));
-}
-// x += alpha p + omega s,  r = s - omega t (into s),  p = r + beta (p - omega v)
-template <int N, typename R>
-TP_HD void bicg_full(cx<R> alpha, cx<R> omega, cx<R> beta, cx<R>* x, cx<R>* p, cx<R>* s, const cx<R>* t, const cx<R>* v) {
-  const bool no_alpha = is_zero(alpha), no_omega = is_zero(omega);
-  const cx<R> ob = cmul(omega, beta);
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    x[c] += cmul(alpha, unless(no_alpha, p[c])) + cmul(omega, unless(no_omega, s[c]));
-    s[c] = s[c] - cmul(omega, unless(no_omega, t[c]));
-    p[c] = s[c] + cmul(beta, p[c]) - cmul(ob, v[c]);
-  }
-}

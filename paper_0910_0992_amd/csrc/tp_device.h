@@ -18,25 +18,25 @@ struct cx {
   R re, im;
 };
 
-template <typename R> TP_HD cx<R> mk(R a, R b) { return cx<R>{a, b}; }
-template <typename R> TP_HD cx<R> operator+(cx<R> a, cx<R> b) { return {a.re + b.re, a.im + b.im}; }
-template <typename R> TP_HD cx<R> operator-(cx<R> a, cx<R> b) { return {a.re - b.re, a.im - b.im}; }
-template <typename R> TP_HD cx<R> operator-(cx<R> a) { return {-a.re, -a.im}; }
-template <typename R> TP_HD cx<R> operator*(R s, cx<R> a) { return {s * a.re, s * a.im}; }
-template <typename R> TP_HD cx<R>& operator+=(cx<R>& a, cx<R> b) { a.re += b.re; a.im += b.im; return a; }
-template <typename R> TP_HD cx<R>& operator-=(cx<R>& a, cx<R> b) { a.re -= b.re; a.im -= b.im; return a; }
-template <typename R> TP_HD cx<R> cmul(cx<R> a, cx<R> b) {
+template <typename R> TP_DEV cx<R> mk(R a, R b) { return cx<R>{a, b}; }
+template <typename R> TP_DEV cx<R> operator+(cx<R> a, cx<R> b) { return {a.re + b.re, a.im + b.im}; }
+template <typename R> TP_DEV cx<R> operator-(cx<R> a, cx<R> b) { return {a.re - b.re, a.im - b.im}; }
+template <typename R> TP_DEV cx<R> operator-(cx<R> a) { return {-a.re, -a.im}; }
+template <typename R> TP_DEV cx<R> operator*(R s, cx<R> a) { return {s * a.re, s * a.im}; }
+template <typename R> TP_DEV cx<R>& operator+=(cx<R>& a, cx<R> b) { a.re += b.re; a.im += b.im; return a; }
+template <typename R> TP_DEV cx<R>& operator-=(cx<R>& a, cx<R> b) { a.re -= b.re; a.im -= b.im; return a; }
+template <typename R> TP_DEV cx<R> cmul(cx<R> a, cx<R> b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 // conj(a) * b
-template <typename R> TP_HD cx<R> cmulc(cx<R> a, cx<R> b) {
+template <typename R> TP_DEV cx<R> cmulc(cx<R> a, cx<R> b) {
   return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
 }
-template <typename R> TP_HD cx<R> conj(cx<R> a) { return {a.re, -a.im}; }
-template <typename R> TP_HD cx<R> ti(cx<R> a) { return {-a.im, a.re}; }   // i a
-template <typename R> TP_HD cx<R> tmi(cx<R> a) { return {a.im, -a.re}; }  // -i a
-template <typename R> TP_HD R norm2(cx<R> a) { return a.re * a.re + a.im * a.im; }
-template <typename R> TP_HD cx<R> czero() { return {R(0), R(0)}; }
+template <typename R> TP_DEV cx<R> conj(cx<R> a) { return {a.re, -a.im}; }
+template <typename R> TP_DEV cx<R> ti(cx<R> a) { return {-a.im, a.re}; }   // i a
+template <typename R> TP_DEV cx<R> tmi(cx<R> a) { return {a.im, -a.re}; }  // -i a
+template <typename R> TP_DEV R norm2(cx<R> a) { return a.re * a.re + a.im * a.im; }
+template <typename R> TP_DEV cx<R> czero() { return {R(0), R(0)}; }
 
 // ---- SU(3) -------------------------------------------------------------------------
 template <typename R>

@@ -354,15 +354,16 @@ enum BlasOp {
 enum BicgSlot {
   BS_RHO = 0,      // rho = <rhat, r> (complex)
   BS_ALPHA = 2,    // alpha = rho / <rhat, v>
-  BS_OMEGA = 4,    // omega = <t, s> / |t|^2
-  BS_BETA = 6,     // beta = (rho_new / rho) (alpha / omega)
   BS_S2 = 8,       // |s|^2
   BS_R2 = 9,       // |r|^2 after the fused update
-  BS_BREAK = 10,   // nonzero: <rhat, v>, |t|^2, omega or rho vanished or is not finite
-  BS_AXPY = 16,    // coefficients (a, b, c) of s = r - alpha v
-  BS_FUSED = 24,   // coefficients (alpha, omega, beta) of the fused update
+  BS_BREAK = 10,   // BicgBreak
+  BS_AXPY = 16,    // coefficients (a, b, c) of s = r - alpha v, and the flag of an op to skip
+  BS_FUSED = 24,   // coefficients (alpha, omega, beta) of the fused update, and its flag
   BS_COUNT = 32
 };
+// Why an iteration ended without its update: <rhat, v> vanished or is not finite; |t|^2, omega or rho
+// did (x and r are then worth the half step x += alpha p, r = s).
+enum BicgBreak { BRK_NONE = 0, BRK_ALPHA = 1, BRK_OMEGA = 2 };
 enum BicgPost { BP_NONE, BP_RHO, BP_ALPHA, BP_S2, BP_OMEGA, BP_R2, BP_ALPHA_ROUNDED, BP_OMEGA_ROUNDED };
 
 struct BlasArgs {

@@ -12,8 +12,8 @@ from oracle.schemes import Operator as OOp
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_scalar_steps_and_updates(tmp_path):
-    """tests/bicg_steps.hip on the host: vanishing, infinite and NaN inner products and vectors."""
+def test_scalar_steps(tmp_path):
+    """tests/bicg_steps.hip on the host: ordinary, vanishing, infinite and NaN inner products."""
     from paper_0910_0992_amd.build import FLAGS, HIPCC
     exe = str(tmp_path / "bicg_steps")
     r = subprocess.run([HIPCC, "-x", "hip", os.path.join(ROOT, "tests", "bicg_steps.hip"), "-o", exe] + FLAGS,
