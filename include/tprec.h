@@ -338,7 +338,8 @@ tp_status tp_solve_multi(tp_op op, const tp_solve_params* params, int32_t nrhs, 
  * Raw form: d L = Re <grad_U, dU>.  TP_FORCE_PROJECTED: G = TH[i U grad_U^dag] with
  * dL/dh = tr(omega G) for U -> exp(i h omega) U, TH = traceless hermitian part.
  * x, lambda: canonical device spinors; grad_links: device complex128
- * [4][Lt][Lz][Ly][Lx][3][3], overwritten. */
+ * [4][Lt][Lz][Ly][Lx][3][3], overwritten.  Works in five FP64 fields (960 bytes per site; two
+ * without the SW part) that the operator keeps and shares with its solves and canonical applies. */
 enum { TP_FORCE_PROJECTED = 1, TP_FORCE_HOPPING_ONLY = 2 };
 tp_status tp_force(tp_op op, const void* x, const void* lambda, void* grad_links, int32_t flags);
 

@@ -153,7 +153,7 @@ Lattice make_lattice(const int32_t d[4]) {
   return L;
 }
 
-Field& tmp_field(tp_op op, int prec, int k) { return ws_get(op, prec, 100 + k); }
+Field& tmp_field(tp_op op, int prec, int k) { return ws_get(op, prec, W_TMP + k); }
 
 }  // namespace
 
@@ -1116,8 +1116,8 @@ tp_status tp_solve(tp_op op, const tp_solve_params* params, void* x, const void*
     set_device(ctx);
     bool l4 = scheme_layout4(P.scheme);
     if (l4 && ctx->lat.L[3] % 2) TP_THROW(TP_EDIMS, "SCHUR4D needs an even time extent");
-    Field& eta64 = ws_get(op, TP_F64, 60);
-    Field& x64 = ws_get(op, TP_F64, 61);
+    Field& eta64 = ws_get(op, TP_F64, W_ETA);
+    Field& x64 = ws_get(op, TP_F64, W_SOL);
     const double2* w = l4 ? nullptr : op->g->w_d;  // p3 schemes solve in the axial frame
     // M^dagger x = eta  <=>  M (g5 x) = g5 eta: g5 on the way in and out
     const bool g5 = P.dagger != 0;

@@ -342,8 +342,8 @@ void launch_force(tp_op op, const double2* x, const double2* lam, double2* grad,
   tp_ctx ctx = op->g->ctx;
   const Lattice& L = ctx->lat;
   ForceArgs a{};
-  Field& xf = ws_get_n(op, TP_F64, W_FORCE, 1);
-  Field& lf = ws_get_n(op, TP_F64, W_FORCE + 1, 1);
+  Field& xf = ws_get_n(op, TP_F64, W_TMP, 1);
+  Field& lf = ws_get_n(op, TP_F64, W_TMP + 1, 1);
   for (int p = 0; p < 2; ++p) {
     a.x[p] = xf.par<double2>(p);
     a.l[p] = lf.par<double2>(p);
@@ -351,7 +351,8 @@ void launch_force(tp_op op, const double2* x, const double2* lam, double2* grad,
   SigmaTab t{};
   if (clover) {
     // two planes of corner fields (36 V/2 doubles) per work field (48 V/2)
-    for (int k = 0; k < 3; ++k) a.Y.p[k] = static_cast<double*>(ws_get_n(op, TP_F64, W_FORCE + 2 + k, 1).data);
+    const int slots[3] = {W_ETA, W_SOL, W_R64};
+    for (int k = 0; k < 3; ++k) a.Y.p[k] = static_cast<double*>(ws_get_n(op, TP_F64, slots[k], 1).data);
     for (int p = 0; p < 6; ++p)
       for (int r = 0; r < 4; ++r)
         for (int q = 0; q < 4; ++q) t.s[p][r][q] = make_double2(sig[p][r][q][0], sig[p][r][q][1]);

@@ -104,7 +104,7 @@ enum {
   W_T1 = 0, W_T2, W_T3, W_T4, W_G5A, W_G5B, W_PREP, W_PREP2,
   // solver vectors
   W_R = 16, W_RHAT, W_P, W_V, W_S, W_T, W_X, W_B, W_Y, W_Z, W_D,
-  W_X64 = 40, W_R64, W_ETA64, W_TMP64,
+  W_TMP64 = 43,
   W_S3W = 48, W_S3F
 };
 

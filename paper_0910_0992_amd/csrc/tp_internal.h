@@ -394,7 +394,6 @@ double finish_norm(tp_ctx ctx, int nblocks);
 // sigma_{mu nu} of planes 03 13 23 01 02 12 (k_force.hip).
 void launch_force(tp_op op, const double2* x, const double2* lam, double2* grad, bool projected, bool clover,
                   const double sig[6][4][4][2]);
-constexpr int W_FORCE = 110;  // first of its five FP64 work fields
 
 // ---------------------------------------------------------------- composite operators (ops.cpp)
 void op_apply_M(tp_op op, int prec, const Field& src, Field& dst, bool dagger);
@@ -408,6 +407,10 @@ void op_prepare(tp_op op, int scheme, int prec, const Field& eta, Field& et);
 void op_reconstruct(tp_op op, int scheme, int prec, const Field& y, Field& x);
 bool scheme_layout4(int scheme);
 // Workspace vectors (allocated lazily, owned by the op).
+// Workspace slots of several entry points, which never run at once on one operator: the true residual,
+// the source and the solution of a single solve, and the two fields of a canonical apply.  The
+// link gradient works in all five.
+enum { W_R64 = 41, W_ETA = 60, W_SOL = 61, W_TMP = 100 };
 // Workspace field `slot` in `prec`, a batch of op->batch_nr fields (1 outside batched
 // operator applications).
 Field& ws_get(tp_op op, int prec, int slot);
