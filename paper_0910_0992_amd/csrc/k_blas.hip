@@ -174,14 +174,10 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
     } else if constexpr (OP == B_NORM2) {
       nt_load_half<S, R>(f0, h, i, x);
       for (int c = 0; c < 6; ++c) acc[0] += double(norm2(x[c]));
-    } else if constexpr (OP == B_DOT || OP == B_DOT_NORM) {
+    } else if constexpr (OP == B_DOT) {
       nt_load_half<S, R>(f0, h, i, x);
       nt_load_half<S, R>(f1, h, i, y);
-      for (int c = 0; c < 6; ++c) {
-        acc[0] += double(x[c].re) * double(y[c].re) + double(x[c].im) * double(y[c].im);
-        acc[1] += double(x[c].re) * double(y[c].im) - double(x[c].im) * double(y[c].re);
-        if constexpr (OP == B_DOT_NORM) acc[2] += double(norm2(y[c]));
-      }
+      dot_acc(x, y, acc);
     } else if constexpr (OP == B_CAXPY_NORM) {
       load_half<S, R>(f0, h, i, x);
       load_half<S, R>(f1, h, i, y);
@@ -232,7 +228,6 @@ __global__ void __launch_bounds__(kBlock) k_blas(BlasK<S> k) {
   constexpr int nred =
       (OP == B_NORM2 || OP == B_CAXPY_NORM || OP == B_AXPYZ_NORM || OP == B_BICG_FUSED) ? 1
       : (OP == B_DOT) ? 2
-      : (OP == B_DOT_NORM) ? 3
       : (OP == B_DOT4_TS) ? 7 : 0;
   if constexpr (nred > 0) block_reduce<nred>(acc, k.partial + (int64_t)rhs * nblk * 8, blk, nblk, rhs, k.fin);
 }
@@ -279,7 +274,6 @@ void finish_go(tp_ctx ctx, int nr, int nb, int nred, int post) {
   switch (nred) {
     case 1: go(k_finish<1>); break;
     case 2: go(k_finish<2>); break;
-    case 3: go(k_finish<3>); break;
     default: go(k_finish<7>); break;
   }
   LAUNCH_CHECK();
@@ -463,7 +457,7 @@ void blas_impl(tp_ctx ctx, BlasOp op, int par0, int npar, std::initializer_list<
   {
     double passes = 2;
     switch (op) {
-      case B_AXPY: case B_XPAY: case B_DOT_NORM: case B_CAXPY_NORM: case B_AXPYZ_NORM: passes = 3; break;
+      case B_AXPY: case B_XPAY: case B_CAXPY_NORM: case B_AXPYZ_NORM: passes = 3; break;
       case B_DOT4_TS: passes = 3; break;
       case B_BICG_FUSED: passes = 8; break;
       case B_NORM2: passes = 1; break;
@@ -482,7 +476,6 @@ void blas_impl(tp_ctx ctx, BlasOp op, int par0, int npar, std::initializer_list<
       case B_XPAY: nb = blas_prec<B_XPAY>(ctx, prec, par0, npar, fs, call); break;
       case B_NORM2: nb = blas_prec<B_NORM2>(ctx, prec, par0, npar, fs, call); nred = 1; break;
       case B_DOT: nb = blas_prec<B_DOT>(ctx, prec, par0, npar, fs, call); nred = 2; break;
-      case B_DOT_NORM: nb = blas_prec<B_DOT_NORM>(ctx, prec, par0, npar, fs, call); nred = 3; break;
       case B_CAXPY_NORM: nb = blas_prec<B_CAXPY_NORM>(ctx, prec, par0, npar, fs, call); nred = 1; break;
       case B_AXPYZ_NORM: nb = blas_prec<B_AXPYZ_NORM>(ctx, prec, par0, npar, fs, call); nred = 1; break;
       case B_DOT4_TS: nb = blas_prec<B_DOT4_TS>(ctx, prec, par0, npar, fs, call); nred = 7; break;

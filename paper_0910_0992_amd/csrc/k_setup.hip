@@ -8,15 +8,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-TP_DEV void canon_coords(int64_t n, const Geom& g, int& x, int& y, int& z, int& t) {
-  x = int(n % g.Lx);
-  int64_t r = n / g.Lx;
-  y = int(r % g.Ly);
-  r /= g.Ly;
-  z = int(r % g.Lz);
-  t = int(r / g.Lz);
-}
-
 // internal (parity, index) of a site for the p3 or p4 layout
 TP_DEV void site_pi(const Geom& g, bool l4, int x, int y, int z, int t, int& p, int64_t& i) {
   int64_t f3 = (int64_t)(x + g.Lx * (y + g.Ly * z));

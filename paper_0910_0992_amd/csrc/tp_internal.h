@@ -339,7 +339,6 @@ enum BlasOp {
   B_XPAY,         // y = x + a y
   B_NORM2,        // |x|^2
   B_DOT,          // <x, y>
-  B_DOT_NORM,     // <x, y>, |y|^2
   B_CAXPY_NORM,   // y = y + a x ; |y|^2
   B_AXPYZ_NORM,   // z = y + a x ; |z|^2            (s = r - alpha v)
   B_DOT4_TS,      // <t, s>, |t|^2, <rhat, s>, <rhat, t>   (fields t, s, rhat)
