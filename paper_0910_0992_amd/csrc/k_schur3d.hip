@@ -327,12 +327,11 @@ struct Sweep {
 // factors' bytes (27 of the 36 columns per slice that two full forward and backward sweeps read),
 // small ones, with fewer wavefronts than SIMDs, by the chain.  (M^ee)^-1 in FP32 at 12^3x64 163 ->
 // 82 us, at 16^3x128 510 -> 215 us, at 24^3x128 849 -> 639 us (4.5 TB/s), against four launches that
-// loaded each step's factors when they needed them.  4 and 8 steps ahead: 6 and 12 are no faster,
-// 8 and 16 take 92 us at 12^3x64.
-template <typename T>
+// loaded each step's factors when they needed them.  kDeep12 steps ahead in sweep 1 (12 columns),
+// kDeep in the others (6): 4 and 8 in FP32 (6 and 12 are no faster, 8 and 16 take 92 us at 12^3x64).
+template <typename T, int kDeep12, int kDeep>
 __global__ __launch_bounds__(64) void k_s3_solve(Sweep<T> a, int64_t V2, Geom g) {
   using R = typename Prec<T>::R;
-  constexpr int kDeep12 = sizeof(T) == 16 ? 2 : 4, kDeep = sizeof(T) == 16 ? 4 : 8;  // steps ahead of sweep 1 (12 columns) and of the others (6)
   __shared__ cx<R> zb[48];
   const SweepLane ln = sweep_lane();
   const int Lt = g.Lt, lane = ln.active ? ln.lane : 0;
@@ -628,8 +627,19 @@ void tinv_impl(tp_op op, int par0, int npar, const Field& src, Field& dst, Field
         a.base_lo[k] = bf.p[1];
       }
     }
-    hipLaunchKernelGGL(k_s3_solve<T>, dim3(L.Vs2 / 4, npar), dim3(64), 0, ctx->stream, a, L.V2, L.g);
-    LAUNCH_CHECK();
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(L.Vs2 / 4, npar), dim3(64), 0, ctx->stream, a, L.V2, L.g);
+      LAUNCH_CHECK();
+    };
+    if constexpr (sizeof(T) == 16) {
+      go(k_s3_solve<T, 2, 4>);
+    } else {
+      // lines no longer than the loads ahead repeat their last slice's: both parities of 32^3x2 86.7 us
+      // with 4 and 8 steps ahead and 53.3 with 2, 32^3x5 154 and 122, 32^3x8 212 and 183 (D_s included);
+      // 32^3x12 293 and 282, 32^3x16 385 and 395, 12^3x16 37.1 and 41.1
+      if (L.L[3] <= 8) go(k_s3_solve<T, 2, 2>);
+      else go(k_s3_solve<T, 4, 8>);
+    }
   }
 }
 }  // namespace

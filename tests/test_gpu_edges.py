@@ -190,3 +190,18 @@ def test_site_kernels_around_the_split(dims, nr, prec):
             ref = (o.prec_dag if dagger else o.prec)(scheme, etas[k])
             assert _rel(y[k], ref) < TOL_LINES[prec], (scheme, dagger, k)
     g.close()
+
+
+# the exact inverse loads its factors 2 steps ahead on FP32 lines of up to 8 slices, 4 and 8 beyond (FP64:
+# 2 and 4)
+@pytest.mark.parametrize("lt", [2, 3, 4, 7, 8, 9, 10, 17])
+@pytest.mark.parametrize("scheme", ["TEMPORAL_SCHUR3D", "TEMPORAL_FULLSW"])
+def test_exact_inverse_of_short_lines(lt, scheme):
+    dims = (4, 2, 4, lt)
+    U, o, g = _make(dims)
+    eta = synth.make_source(dims, 2107)
+    t = torch.from_numpy(eta).cuda()
+    for prec in ("F64", "F32"):
+        assert _rel(g.apply_prec(t, scheme, prec), o.prec(scheme, eta)) < TOL_LINES[prec], prec
+        assert _rel(g.apply_prec(t, scheme, prec, dagger=True), o.prec_dag(scheme, eta)) < TOL_LINES[prec], prec
+    g.close()
