@@ -41,14 +41,20 @@ TP_DEV uint32_t tile_block(const TileOrder& o, uint32_t b) {
 
 // Measured rules.  Tiles, against plain: 4-19% faster hops in F32 and F16N at 16^3x128, 24^3x128
 // and (F32) 32^3x256, but 2-5% slower for FP16 storage with four chunks per tile (256-slice
-// lines), which keeps the plain order.  Parts, where the launch has no whole tiles, against plain:
-// F32 hop at 14x14x12x107 27.6 -> 16.3 us, at 24^3x120 (3.3 MB of neighbour spinors a plane) 125 ->
-// 99, FP64 residual at 20x20x22x46 (1.8 MB) 123 -> 108, but at 24^3x120 (6.6 MB) 411 -> 433 and F16N
-// with 12 right-hand sides at 16^3x128 (11 MB) 117 -> 121: parts up to 6 MB a plane.
-TileOrder tile_order(const Lattice& L, int64_t nblocks, int nr, double spinor) {
+// lines), which keeps the plain order.  Parts, where the launch has no whole tiles, while the
+// neighbour spinors of a plane stay below
+//   6 MB without the clover term: D_s, plain and parts in us, F32 14x14x12x107 27.6 and 16.3, F64
+//     24^3x84 (4.6 MB) 179 and 153, 24^3x107 (5.9 MB) 239 and 198, F16N 32^3x160 (4.6 MB) 177 and 171
+//     (batches of 12 right-hand sides, F16N 16^3x128, 11 MB: 117 and 121);
+//   4.2 MB (FP16 storage: 2.5 MB) with it, whose blocks pass through the same L2: D_s and A, F64 24^3x72
+//     (4.0 MB) gains 5%, 24^3x84 (4.6 MB) 252 and 250 or 243 and 248, 32^3x60 (5.9 MB) 397 and 432; F32
+//     32^3x75 (3.7 MB) 259 and 254, 32^3x88 (4.3 MB) 299 and 304; F16N 32^3x80 (2.3 MB) 138 and 132, 48^3x40
+//     (2.6 MB) 210 and 223, 40^3x80 (3.6 MB) 265 and 281.
+TileOrder tile_order(const Lattice& L, int64_t nblocks, int nr, double spinor, bool clov) {
   TileOrder o{1, 1, 1, 1, 0, kOrderPlain};
   const Geom& g = L.g;
-  if (double(g.Lxh) * g.Ly * g.Lt * nr * spinor <= 6e6) o.mode = kOrderParts;
+  const double most = !clov || nr != 1 ? 6e6 : (spinor < 60 ? 2.5e6 : 4.2e6);
+  if (double(g.Lxh) * g.Ly * g.Lt * nr * spinor <= most) o.mode = kOrderParts;
   if (nr != 1 || int64_t(nblocks) * kBlock != g.V2) return o;
   if (g.Lt % 64 || (8 % (g.Lt / 64)) || g.Lxh % kTile) return o;
   const uint32_t Q = uint32_t(g.Lt / 64), tiles = uint32_t(g.Vs2 / kTile);
@@ -407,7 +413,7 @@ int site_t(tp_op op, const SiteIO& io, Field& dst, SiteCoef cf, int ck, int par0
   if (norm && a.nr != 1) TP_THROW(TP_EINVAL, "a fused norm needs a single right-hand side");
   int64_t nb = (L.V2 + kBlock - 1) / kBlock;
   if (norm) nb = std::min<int64_t>(nb, kRedBlocks / 2);
-  a.ord = tile_order(L, nb, a.nr, 2.0 * Field::half_bytes(dst.prec));
+  a.ord = tile_order(L, nb, a.nr, 2.0 * Field::half_bytes(dst.prec), clov);
   bool dt = cf.c_t != 0.0, ds = cf.c_s != 0.0;
   bool i2 = in2 != nullptr;
   // spatial hops read SU(3) links as two rows (FP64: only links SU(3) to 1e-13)

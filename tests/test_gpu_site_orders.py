@@ -19,29 +19,32 @@ TOL = {"F64": (1e-12, 1e-12), "F32": (6e-6, 2e-5), "F16N": (4e-3, 1.5e-2)}
 XI, M0, CS, CT = 3.5, -0.05, 1.6 / 3.5, 1.0
 
 
-def _order(dims, prec, nr=1):
-    """The rule of tile_order: which workgroup order a launch takes."""
+def _order(dims, prec, clover):
+    """The rule of tile_order for one field: which workgroup order a launch takes."""
     lx, ly, lz, lt = dims
     v2, spinor = int(np.prod(dims)) // 2, {"F64": 192, "F32": 96, "F16N": 56}[prec]
     q = lt // 64
-    if nr == 1 and v2 % 256 == 0 and lt % 64 == 0 and q and 8 % q == 0 and (lx // 2) % 4 == 0:
+    if v2 % 256 == 0 and lt % 64 == 0 and q and 8 % q == 0 and (lx // 2) % 4 == 0:
         tiles = lx // 2 * ly * lz // 4
         if tiles * q % 8 == 0:
             return "plain" if prec == "F16N" and q >= 4 else "tiles"
-    return "parts" if lx // 2 * ly * lt * nr * spinor <= 6e6 else "plain"
+    most = 6e6 if not clover else (2.5e6 if prec == "F16N" else 4.2e6)
+    return "parts" if lx // 2 * ly * lt * spinor <= most else "plain"
 
 
 # one, two, four and eight workgroups per tile, two tiles and one per x row, several z blocks; then
-# lattices without whole tiles (parts), and plain by its size in FP64 (7.4 MB a plane)
-ORDERS = [((16, 8, 12, 64), "tiles"), ((16, 8, 8, 128), "tiles"), ((16, 4, 8, 256), "tiles"), ((8, 8, 4, 512), "tiles"),
-          ((12, 10, 10, 66), "parts"), ((24, 24, 2, 134), "plain")]
+# lattices without whole tiles: parts, parts for D_s alone (5.5 MB a plane in FP64) and plain (7.4 MB)
+ORDERS = [((16, 8, 12, 64), "tiles", "tiles"), ((16, 8, 8, 128), "tiles", "tiles"), ((16, 4, 8, 256), "tiles", "tiles"),
+          ((8, 8, 4, 512), "tiles", "tiles"), ((12, 10, 10, 66), "parts", "parts"), ((24, 24, 2, 100), "parts", "plain"),
+          ((24, 24, 2, 134), "plain", "plain")]
 
 
-@pytest.mark.parametrize("dims,order", ORDERS)
+@pytest.mark.parametrize("dims,hop,clover", ORDERS)
 @pytest.mark.parametrize("links", ["SU(3)", "U(3)"])
-def test_site_kernels_in_every_order(dims, order, links):
+def test_site_kernels_in_every_order(dims, hop, clover, links):
     from paper_0910_0992_amd import Operator
-    assert int(np.prod(dims)) // 2 > SPLIT_SITES and _order(dims, "F64") == order
+    assert int(np.prod(dims)) // 2 > SPLIT_SITES
+    assert (_order(dims, "F64", False), _order(dims, "F64", True)) == (hop, clover)
     U = synth.make_links(dims, 0.35, 0.12, 1000)
     if links == "U(3)":
         U[:3] *= np.exp(0.4j)
@@ -50,7 +53,7 @@ def test_site_kernels_in_every_order(dims, order, links):
     eta = synth.make_source(dims, 2000)
     refs = {s: o.prec(s, eta) for s in ("UNPREC", "TEMPORAL_SCHUR")}
     for prec in ("F64", "F32", "F16N"):
-        print(f"[order] {dims} {links} {prec} {_order(dims, prec)}", flush=True)
+        print(f"[order] {dims} {links} {prec} {_order(dims, prec, False)} {_order(dims, prec, True)}", flush=True)
         f = g.to_field(torch.from_numpy(eta).cuda(), "P3", prec)
         for k, (scheme, ref) in enumerate(refs.items()):
             y = g.from_field(g.apply_prec_field(f, scheme))[0].cpu().numpy()
