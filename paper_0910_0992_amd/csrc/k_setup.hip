@@ -47,7 +47,7 @@ TP_DEV void rotate_spinor(const double2* __restrict__ w, int p, int64_t i, int64
 // written through LDS, so that a wavefront stores whole lines instead of 16 bytes of 64 sites.
 // In canonical order (runs of 64 bytes) pack and unpack took 228 and 255 us at 24^3x128 (F64), 187
 // and 176 us now (5.0 and 5.3 TB/s); unpack without LDS 253 us.  Which order pack takes: see
-// pack_in_canonical_order.
+// pack_order.
 struct PackSite {
   int64_t n, i;  // canonical site; index in the layout
   int p;         // parity in the layout
@@ -73,11 +73,11 @@ TP_DEV PackSite pack_site(const Geom& g, bool l4) {
   return r;
 }
 
-// The same for a thread per site in canonical order.
+// The same for a thread per site in canonical order (parts: of which each XCD takes a contiguous part).
 constexpr int kPackCanon = 256;
-TP_DEV PackSite pack_site_canon(const Geom& g, bool l4) {
+TP_DEV PackSite pack_site_canon(const Geom& g, bool l4, bool parts) {
   PackSite r;
-  r.n = (int64_t)blockIdx.x * kPackCanon + threadIdx.x;
+  r.n = (int64_t)(parts ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x) * kPackCanon + threadIdx.x;
   r.ok = r.n < 2 * g.V2;
   const int x = int(r.n % g.Lx);
   int64_t q = r.n / g.Lx;
@@ -95,9 +95,9 @@ TP_DEV PackSite pack_site_canon(const Geom& g, bool l4) {
 template <typename S, bool CANON>
 __global__ void __launch_bounds__(CANON ? kPackCanon : kPack) k_pack(const double2* __restrict__ canon, SpinorF<S> f0, SpinorF<S> f1,
                                                  Geom g, bool l4, bool g5,
-                                                 const double2* __restrict__ w) {
+                                                 const double2* __restrict__ w, bool parts) {
   using R = typename Prec<S>::R;
-  const PackSite q = CANON ? pack_site_canon(g, l4) : pack_site(g, l4);
+  const PackSite q = CANON ? pack_site_canon(g, l4, parts) : pack_site(g, l4);
   if (!q.ok) return;
   cx<double> d[12];
   const double2* src = canon + q.n * 12;
@@ -716,29 +716,39 @@ __global__ void __launch_bounds__(kBlock) k_plaquette_sum(double* part, int64_t 
 
 inline unsigned nblk(int64_t n, int64_t b = kBlock) { return (unsigned)((n + b - 1) / b); }
 
-// Into p4, where canonical order is that of the planes, sub-blocks only shorten the runs: F64 32^3x128
-// 322 and 295 us, 32^3x6 15.8 and 12.5, F32 40^3x48 185 and 161 (sub-blocks and canonical order).  Into
-// p3 they pay (F64 24^3x128 186 and 247 us, 32^3x4 11.0 and 11.7) but for
+// Up to 65536 sites sub-blocks always: they leave a site in the L2 of the XCD whose next kernel reads
+// it (a 4D even-odd apply at 8^3x32, F64: 30.4 us, 31.7 with canonical order, 30.9 with its parts).
+// Beyond, into p4, where canonical order is that of the planes and sub-blocks only shorten the runs (in
+// us: sub-blocks, canonical order, its parts):
+//   parts up to 2^20 sites, for the same reason (F64 16^3x128 31.4, 35.4, 30.7 and the apply 380, 383, 378;
+//     32^3x32 82.8, 81.5, 78.5 and 875, 884, 868), plain beyond (32^3x128 321, 295, 306 and 3062, 3045, 3055; F32
+//     40^3x48 188, 160, 167).
+// Into p3 sub-blocks pay (F64 24^3x128 186 and 247 us, 32^3x4 11.0 and 11.7) but for
 //   lines of 5 to 27 slices that are no multiple of four, whose last slices leave sub-blocks part
 //     empty: 32^3x5 20.2 and 16.3, 32^3x14 41.8 and 38.3, F32 32^3x18 41.9 and 39.8 (but F64 32^3x26 93
-//     and 99; 32^3x3 8.7 and 9.6, 32^3x33 138 and 145);
+//     and 99; 32^3x3 8.7 and 9.6, 32^3x33 138 and 145; parts 32^3x5 18.1, 32^3x14 47.0);
 //   odd lines of 64 slices or more in a field that outgrows the last-level cache (256 MB): their runs
 //     start in the middle of a cache line, whose halves are then written to memory apart: 24^3x107
 //     203 and 195 us (24^3x106: 159 and 191), F32 32^3x65 228 and 212, but 16^3x255 123 and 159.
-bool pack_in_canonical_order(const Lattice& L, bool l4) {
+enum PackOrder { kPackSub, kPackPlain, kPackParts };
+PackOrder pack_order(const Lattice& L, bool l4) {
   const int Lt = L.L[3];
-  return l4 || (Lt > 4 && Lt < 28 && Lt % 4) || (Lt % 2 && Lt >= 64 && double(L.V) * 192.0 > 256e6);
+  if (L.V <= (1 << 16)) return kPackSub;
+  if (l4) return L.V <= (1 << 20) ? kPackParts : kPackPlain;
+  if (Lt > 4 && Lt < 28 && Lt % 4) return kPackPlain;
+  return Lt % 2 && Lt >= 64 && double(L.V) * 192.0 > 256e6 ? kPackPlain : kPackSub;
 }
 template <typename S>
 void pack_t(tp_ctx ctx, const double2* canon, Field& dst, bool l4, bool g5, const double2* w) {
   const Lattice& L = ctx->lat;
   const SpinorF<S> f0 = dst.template par<S>(0), f1 = dst.template par<S>(1);
-  if (pack_in_canonical_order(L, l4))
-    hipLaunchKernelGGL((k_pack<S, true>), dim3(nblk(L.V, kPackCanon)), dim3(kPackCanon), 0, ctx->stream, canon, f0, f1,
-                       L.g, l4, g5, w);
-  else
+  const PackOrder o = pack_order(L, l4);
+  if (o == kPackSub)
     hipLaunchKernelGGL((k_pack<S, false>), dim3(sub_blocks(L) / 2), dim3(kPack), 0, ctx->stream, canon, f0, f1, L.g,
-                       l4, g5, w);
+                       l4, g5, w, false);
+  else
+    hipLaunchKernelGGL((k_pack<S, true>), dim3(nblk(L.V, kPackCanon)), dim3(kPackCanon), 0, ctx->stream, canon, f0, f1,
+                       L.g, l4, g5, w, o == kPackParts);
   LAUNCH_CHECK();
 }
 template <typename S>
