@@ -30,27 +30,27 @@ TRAFFIC = {
     ("clover_32x256", "F16N", "ilu_mid"): {
         "bytes_per_launch": 1.5486e+09,
         "sources": ["k_line_impl.h", "k_line_f16.hip", "k_line.hip", "tp_device.h"],
-        "sha256": "e4e82d73bf07cecaaf8bc165b14485db4e432c40abe7333b9aaab6574c6ed081",
+        "sha256": "eacd6726fb61c47c667d21de13b9cb497f5a62ad4f227281c766cb1ef7034504",
     },
     ("clover_32x256", "F16N", "hop_clover"): {
-        "bytes_per_launch": 2.6816e+09,
+        "bytes_per_launch": 2.6810e+09,
         "sources": ["k_site.hip", "tp_hop.h", "tp_device.h"],
-        "sha256": "d18bafc7974e8dfdbfc7b3bd865e54ef966085d828cb9834190d4dafef9ff27e",
+        "sha256": "d9b6184bc5dd03b4d9d8c05c2c9fc5cf89bb75c163110b7c8503e8521ce31d6d",
     },
     ("clover_32x256", "F16N", "hop_ds"): {
-        "bytes_per_launch": 1.6863e+09,
+        "bytes_per_launch": 1.6917e+09,
         "sources": ["k_site.hip", "tp_hop.h", "tp_device.h"],
-        "sha256": "d18bafc7974e8dfdbfc7b3bd865e54ef966085d828cb9834190d4dafef9ff27e",
+        "sha256": "d9b6184bc5dd03b4d9d8c05c2c9fc5cf89bb75c163110b7c8503e8521ce31d6d",
     },
     ("clover_32x256", "F16N", "blas_bicg_fused"): {
         "bytes_per_launch": 3.7582e+09,
-        "sources": ["k_blas.hip", "tp_device.h"],
-        "sha256": "68235116c321e6ff0aded0b254187495fa7107cc206b6c846ec0fc7f92137da6",
+        "sources": ["k_blas.hip", "tp_bicg.h", "tp_device.h"],
+        "sha256": "20958604a968403f8c168be616189909c8bf580f917324d580d052aef8bb28a0",
     },
     ("clover_32x256", "F16N", "scan_cl"): {
         "bytes_per_launch": 7.0949e+08,
         "sources": ["k_line_impl.h", "k_line_f16.hip", "k_line.hip", "tp_device.h"],
-        "sha256": "e4e82d73bf07cecaaf8bc165b14485db4e432c40abe7333b9aaab6574c6ed081",
+        "sha256": "eacd6726fb61c47c667d21de13b9cb497f5a62ad4f227281c766cb1ef7034504",
     },
 }
 

@@ -138,8 +138,8 @@ tp_status tp_ctx_device_bytes(tp_ctx ctx, size_t* bytes);
  * work in the axial frame rotated by W^dag (Sec. II.C), a gauge rotation only for
  * unitary W.  Spatial links may be any complex 3x3 matrices; when all of them are
  * SU(3) to 1e-9, the FP32 and FP16 kernels read their first two rows and rebuild
- * the third (FP64 kernels always read all nine entries).  Links containing NaN or
- * Inf are refused with TP_EINVAL. */
+ * the third (to 1e-13, the FP64 spatial hops of the p3 operators too).  Links containing
+ * NaN or Inf are refused with TP_EINVAL. */
 tp_status tp_gauge_create(tp_ctx ctx, const void* links, int32_t where, tp_gauge* out);
 tp_status tp_gauge_destroy(tp_gauge g);
 /* Mean plaquette diagnostics: spatial and temporal (1/3 Re tr) averages. */

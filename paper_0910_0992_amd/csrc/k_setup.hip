@@ -212,9 +212,10 @@ __global__ void __launch_bounds__(64) k_wline(const double2* __restrict__ canon,
 // operator) with the phase b folded into U_t(Lt-1), and p3 planes (F64, F32, F16) of the
 // axial-gauge links U^ax_mu(x) = W(x)^dag U'_mu(x) W(x+mu) with Omega = W^dag (Sec. II.C, App. C):
 // every time link becomes the identity except U^ax_t(Lt-1) = W(0) = P.  A workgroup handles the
-// 64 sites of a sub-block, wavefront mu one direction; bound by what it writes (1872 bytes per
-// site; 24^3x128: 2.9 ms in three kernels in canonical order, whose planes took 16 and 64 bytes
-// at a time).
+// 64 sites of a sub-block, wavefront mu one direction, so that planes and W are runs of 256 bytes;
+// the caller's links are nine loads whose lanes lie 144 bytes apart.  At 24^3x128 1.58 ms, 2.75 TB/s of
+// the 2448 bytes per site that it cannot do without (1872 of them written); 2.9 ms in three kernels
+// in canonical order, whose planes took 16 and 64 bytes at a time.
 __global__ void __launch_bounds__(256) k_links(const double2* __restrict__ canon, const double2* __restrict__ wd,
                                                double2* u3d, float2* u3f, __half2* u3h, double2* u4d, float2* u4f,
                                                Geom g, int64_t V, double b, int* flags) {

@@ -117,8 +117,7 @@ template <> TP_DEV void ld2<float, float2>(const float2* p, cx<float>& a, cx<flo
 }
 struct alignas(8) Half2x2 { __half2 a, b; };
 
-// Loads of 8, 12 and 16 bytes, plain or with the non-temporal hint (fields read once, in passes
-// larger than the caches).
+// Loads of 8, 12 and 16 bytes, plain or with the non-temporal hint (fields that a pass reads once).
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT, typename T> TP_DEV T ld_vec(const T* p) {
